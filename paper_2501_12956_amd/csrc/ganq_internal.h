@@ -139,7 +139,7 @@ hipError_t launch_pair_split(hipStream_t s, const float* X, int64_t rows, int64_
                              _Float16* dst, int* ex);
 hipError_t launch_pair_gemm(hipStream_t s, const _Float16* A, const _Float16* B, int64_t M, int64_t N, int64_t kp,
                             int step0, int step1, int splits, const int* ea, const int* eb, float* C, int64_t ldc,
-                            int64_t cstride);
+                            int64_t cstride, bool small_tiles);
 size_t pair_syrk256_scratch_bytes(int64_t M);
 hipError_t launch_pair_syrk256(hipStream_t s, int64_t M, const float* A, int64_t lda, float* C, int64_t ldc,
                                void* scratch);

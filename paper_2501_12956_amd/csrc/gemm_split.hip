@@ -23,6 +23,7 @@ namespace ganq {
 namespace {
 
 constexpr int PLINE = 128;       // bytes of one row's line: 32 hi, 32 lo
+constexpr int FLUSH = 8;         // steps of 32 columns that one accumulator of the small tiles sums
 
 // One workgroup per row: the exponent that brings the row's largest finite magnitude near 2^14, and
 // the row's pieces, zero for cols <= k < kp.  The second pass over the row finds it in the cache.
@@ -135,10 +136,11 @@ __global__ __launch_bounds__(TILE * 2, 2) void pair_gemm_kernel(const _Float16* 
     }
   };
 
-  // The small tiles have registers for a second set of accumulators: the cross products, 2^-11 of the
-  // others, then round among themselves and the main chain is a third as long.
+  // The small tiles have registers for two more sets of accumulators.  The cross products, 2^-11 of the
+  // others, round among themselves, and every FLUSH steps the main sum moves to a total of its own: the
+  // rounding of an fp32 accumulator grows with the length and the size of what it has summed.
   constexpr bool TWO = TILE == 128;
-  floatx16 acc[TI][TJ], crs[TWO ? TI : 1][TWO ? TJ : 1];
+  floatx16 acc[TI][TJ], crs[TWO ? TI : 1][TWO ? TJ : 1], tot[TWO ? TI : 1][TWO ? TJ : 1];
 #pragma unroll
   for (int i = 0; i < TI; ++i)
 #pragma unroll
@@ -146,7 +148,7 @@ __global__ __launch_bounds__(TILE * 2, 2) void pair_gemm_kernel(const _Float16* 
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         acc[i][j][v] = 0.f;
-        if constexpr (TWO) crs[i][j][v] = 0.f;
+        if constexpr (TWO) crs[i][j][v] = tot[i][j][v] = 0.f;
       }
 
   const int rswz = l32 & 7;
@@ -157,6 +159,19 @@ __global__ __launch_bounds__(TILE * 2, 2) void pair_gemm_kernel(const _Float16* 
     wait_all_loads();
     __syncthreads();
     if (s + 1 < se) issue(s + 1, st ^ 1);
+    if constexpr (TWO) {
+      if (s > sb && (s - sb) % FLUSH == 0) {
+#pragma unroll
+        for (int i = 0; i < TI; ++i)
+#pragma unroll
+          for (int j = 0; j < TJ; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+              tot[i][j][v] += acc[i][j][v];
+              acc[i][j][v] = 0.f;
+            }
+      }
+    }
     const unsigned char* Asm = gsm + st * STAGEB + (wr * (TILE / 2) + l32) * PLINE;
     const unsigned char* Bsm = gsm + st * STAGEB + TILEB + (wc * 64 + l32) * PLINE;
 #pragma unroll
@@ -213,7 +228,7 @@ __global__ __launch_bounds__(TILE * 2, 2) void pair_gemm_kernel(const _Float16* 
       for (int j = 0; j < TJ; ++j) {
         const int64_t col = n0 + wc * 64 + j * 32 + l32;
         float r = acc[i][j][v];
-        if constexpr (TWO) r += crs[i][j][v];
+        if constexpr (TWO) r = tot[i][j][v] + (r + crs[i][j][v]);
         if (col < N) Cs[row * ldc + col] = ldexpf(r, -(e + ebj[j]));
       }
     }
@@ -373,14 +388,19 @@ hipError_t launch_pair_split(hipStream_t s, const float* X, int64_t rows, int64_
 
 // C + sp * cstride (sp < splits) = the share of split sp of the sum over the 32-column steps
 // [step0, step1) of A B^T, both given as piece matrices with rows of 2 kp halves.
+// small_tiles: 128 x 128 tiles, whose sums are the more accurate ones (FLUSH); the S-update asks for them.
+// Mean error of its targets in units of 2^-24 of their size, with sums of everything to the right in
+// the fp32 matrix units / with large tiles (m = 8192) / now: 5000 columns 5.5 / 6.3 / 1.7, with the
+// dominant features on the left 2.7 / 8.1 / 2.0; 27648 columns 11.6 / 10.7 / 2.1.  It costs 2.4 of the
+// 22.4 ms of an 8192 x 28672 sweep.  Otherwise
 // 256 x 256 tiles where they give at least 3 of 4 compute units one; below that 128 x 128 tiles:
 // 2048 x 2048 products have 64 of the large tiles and take 141 us with
 // them, 66 us with 256 of the small ones (a tile's K walk is the same length either way).
 hipError_t launch_pair_gemm(hipStream_t s, const _Float16* A, const _Float16* B, int64_t M, int64_t N, int64_t kp,
                             int step0, int step1, int splits, const int* ea, const int* eb, float* C, int64_t ldc,
-                            int64_t cstride) {
+                            int64_t cstride, bool small_tiles) {
   hipError_t e;
-  if (ceil_div(M, 256) * ceil_div(N, 256) * splits >= 192) {
+  if (!small_tiles && ceil_div(M, 256) * ceil_div(N, 256) * splits >= 192) {
     constexpr int lds = 4 * 256 * PLINE;
     static std::atomic<uint64_t> lds_set{0};
     if ((e = ensure_dynamic_lds((const void*)pair_gemm_kernel<256>, lds, lds_set)) != hipSuccess) return e;
@@ -416,7 +436,7 @@ hipError_t launch_gemm_split(hipStream_t s, int64_t M, int64_t N, int64_t K, con
   if ((e = launch_pair_split(s, A, M, K, lda, As, ea)) != hipSuccess) return e;
   if ((e = launch_pair_split(s, B, N, K, ldb, Bs, eb)) != hipSuccess) return e;
   const int64_t kp = pair_columns(K);
-  return launch_pair_gemm(s, As, Bs, M, N, kp, 0, (int)(kp / 32), 1, ea, eb, C, ldc, 0);
+  return launch_pair_gemm(s, As, Bs, M, N, kp, 0, (int)(kp / 32), 1, ea, eb, C, ldc, 0, false);
 }
 
 size_t pair_syrk256_scratch_bytes(int64_t M) {

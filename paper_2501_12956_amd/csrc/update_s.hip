@@ -34,7 +34,7 @@
 // the products (3 m n^2 flops on the fp16 units).
 // Measured per sweep, before (one workgroup walking all n columns, its sums over everything to the
 // right on the fp32 matrix units) and now: 4096 x 4096 0.94 -> 0.53 ms (87 us of sweep and 60 us of
-// products per super-block), 4096 x 11008 5.4 -> 2.5 ms, 8192 x 28672 71.4 -> 20.8 ms, 256 x 512
+// products per super-block), 4096 x 11008 5.4 -> 2.5 ms, 8192 x 28672 71.4 -> 24.8 ms, 256 x 512
 // 62 -> 38 us.
 #include "ganq_internal.h"
 
@@ -47,7 +47,7 @@ constexpr int PU = 12;          // k steps of 32 in flight per multiplying wavef
 constexpr int NW = 8;           // wavefronts per workgroup: 4 decide, 4 multiply
 constexpr int NP = 4;
 constexpr int WSB = 1024;       // columns per super-block
-constexpr int WSPLIT = 4;       // most k-splits of a product
+constexpr int WSPLIT = 2;       // most k-splits of a product
 constexpr int LF_COLS16 = WSB / 32 * 2 * 512;   // halves of LF per 16 columns: [k step][piece][lane][8 k]
 
 // One super-block: the sums over the columns right of it are in F (nsplit partial sums, rows of
@@ -660,16 +660,12 @@ hipError_t launch_update_S(hipStream_t s, const float* W, int64_t m, int64_t n, 
     sb.eb = sc.eb;
     if (sb.jhi < n) {
       const int s0 = (int)(sb.jhi / 32), s1 = (int)(kp / 32);
-      // Two k-splits where one would leave compute units idle (the product then takes its small tiles) and
-      // they still have 16 steps each.  With large tiles, no split sums more than 4096 columns (up to four
-      // splits): they have no registers for separate cross products, and the rounding of an fp32
-      // accumulator grows with the length of its chain.
-      const int64_t steps = s1 - s0, tiles = ceil_div(m, 256) * (WSB / 256);
-      int64_t split = (steps >= 32 && tiles < 192) ? 2 : 1;
-      if (tiles * split >= 192 && split < ceil_div(steps, 128)) split = ceil_div(steps, 128);
-      sb.nsplit = (int)(split < WSPLIT ? split : WSPLIT);
+      // Two k-splits where one gives no more than a tile per compute unit, which holds two, and they still
+      // have 16 steps each.  8192 x 8192 with one split 2.85 ms, with two 2.94; 4096 rows with one leave
+      // half the slots empty.
+      sb.nsplit = (s1 - s0 >= 32 && ceil_div(m, 128) * (WSB / 128) <= 256) ? 2 : 1;
       if ((e = launch_pair_gemm(s, sc.Ep, sc.LT + jlo * 2 * kp, m, WSB, kp, s0, s1, sb.nsplit, sc.ea, sc.eb + jlo,
-                                sc.F, WSB, sb.fstride)) != hipSuccess) return e;
+                                sc.F, WSB, sb.fstride, true)) != hipSuccess) return e;
     }
     if (vec)
       hipLaunchKernelGGL(update_S_kernel<true>, grid, block, S_LDS_BYTES, s, W, m, n, ldw, L, ldl, sc.rdiag, T, C, Q,
