@@ -269,9 +269,11 @@ __global__ __launch_bounds__(256) void pair_split256_kernel(const float* __restr
 
 // 128 x 128 tiles on or below the diagonal, 4 wavefronts of 64 x 64, all 256 columns in eight steps
 // through two LDS stages, two workgroups per compute unit.  The cross products have accumulators of
-// their own; the product of the low pieces (a sum of squares on the diagonal) changes nothing in
-// |L L^T - H| (2.2e-7 at n = 6000, with it as without) and is dropped here as well.  Bound by C: 128 KB
-// of it move per tile against 2.6 us of MFMA.  Factorization on its own, fp32 matrix units before:
+// their own.  The product of the low pieces is dropped except in the diagonal tiles: there it is a sum of
+// squares, 1.5e-8 of H_jj that every pivot would keep (where the pivots shrink to 1 / 17 of H_jj their
+// relative error was 1.6 times that of the fp32 update; with it, and in |L L^T - H| anyway, the errors are
+// level or lower).  Bound by C: 128 KB of it move per tile against 2.6 us of MFMA.  Factorization on
+// its own, fp32 matrix units before:
 // n = 28672 94.6 -> 57.0 ms, 11008 10.0 -> 7.9 ms, 8192 5.85 -> 5.1 ms.
 __global__ __launch_bounds__(256, 2) void pair_syrk256_kernel(const _Float16* __restrict__ A, int64_t M,
                                                               const int* __restrict__ ea, float* __restrict__ C,
@@ -346,6 +348,12 @@ __global__ __launch_bounds__(256, 2) void pair_syrk256_kernel(const _Float16* __
       for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j) crs[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah[i], bl[j], crs[i][j], 0, 0, 0);
+      if (bm == bn) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j) crs[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(al[i], bl[j], crs[i][j], 0, 0, 0);
+      }
     }
   }
   const bool full = (m0 + TILE <= M) && (bn < bm);
