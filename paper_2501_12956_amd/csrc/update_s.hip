@@ -144,12 +144,15 @@ struct Step {
       __builtin_amdgcn_sched_barrier(0);
       accn[0] = fmaf(ep, prev.x.x, accn[0]);
       const float cand = row_bcast<co>(Wr[qo]) - ts;
+      float cand0 = (c == 0) ? cand : 0.f;
+      asm("" : "+v"(cand0));
       __builtin_amdgcn_sched_barrier(0);
       const float tg = row_bcast<co>(tl);
-      const unsigned long long upto = __builtin_amdgcn_ballot_w64(tg <= hi), from = __builtin_amdgcn_ballot_w64(tg > lo);
-      float x = (tg > lo) ? cand : 0.f;
-      asm("" : "+v"(x));      // two selects: combining the masks first would take a detour over the scalar unit
-      x = (tg <= hi) ? x : 0.f;
+      // lane 0 holds for every target that is not above its midpoint; for -inf and NaN there is no vote
+      const unsigned long long upto = __builtin_amdgcn_ballot_w64(!(tg > hi)), from = __builtin_amdgcn_ballot_w64(tg > lo);
+      float x = (tg > lo) ? cand : cand0;
+      asm("" : "+v"(x));      // selects one after the other: combining masks would take a detour over the scalar unit
+      x = (tg > hi) ? 0.f : x;
       __builtin_amdgcn_sched_barrier(0);
       accn[1] = fmaf(ep, prev.x.y, accn[1]);
       accn[2] = fmaf(ep, prev.x.z, accn[2]);
@@ -325,8 +328,11 @@ __global__ __launch_bounds__(64 * NW) void update_S_kernel(const float* __restri
 
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
+        // an infinite residual or NaN goes into the low piece alone: every product of it is then one with
+        // L's high piece, infinite or NaN as in fp32 (inf in the high piece would meet a low piece of L
+        // that is zero or of the other sign)
         const float v = ldexpf(Er[q], ea);
-        const _Float16 hi = (_Float16)v;
+        const _Float16 hi = (_Float16)((fabsf(v) < __builtin_huge_valf()) ? v : 0.f);
         const int at = ((b * 8 + 2 * q + (c >> 3)) * SR + r) * 8 + (c & 7);
         Eh[at] = hi;
         Elo[at] = (_Float16)(v - (float)hi);
@@ -390,7 +396,7 @@ __global__ __launch_bounds__(64 * NW) void update_S_kernel(const float* __restri
         uint32_t q4 = 0u;
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-          // the lane of this row that the column's step chose (none for a target that is not a number)
+          // the lane of this row that the column's step chose; no vote means the lowest code
           const unsigned long long v = votes[((b & 1) * NP + (orow >> 2)) * SB + oc + u];
           const uint32_t v16 = (uint32_t)(v >> (16 * (orow & 3))) & 0xffffu;
           const int q = repl[orow * 16 + (v16 != 0u ? __builtin_ctz(v16) : 0)];
@@ -539,7 +545,7 @@ __global__ __launch_bounds__(256) void l_pieces_kernel(const float* __restrict__
 #pragma unroll
   for (int u = 0; u < 16; ++u) {
     const float v = ldexpf(tile[kq + u][jj], e);
-    const _Float16 h = (_Float16)v;
+    const _Float16 h = (_Float16)((fabsf(v) < __builtin_huge_valf()) ? v : 0.f);      // as for the residuals
     hi[u >> 3][u & 7] = h;
     lo[u >> 3][u & 7] = (_Float16)(v - (float)h);
   }

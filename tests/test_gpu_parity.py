@@ -1035,3 +1035,31 @@ def test_update_T_at_the_edges_of_slabs_and_stages(ctx, m, n, nbits):
     Tref, _ = ref.update_T(W.numpy().astype(np.float64), H32.numpy().astype(np.float64), Q.numpy(), nbits)
     err = np.abs(T - Tref).max(axis=1) / np.abs(Tref).max(axis=1)
     assert err.max() <= 1e-4, err.max()
+
+
+@pytest.mark.parametrize("n,events", [(130, (100,)), (1000, (990, 500)), (2200, (2150, 1500, 700))])
+def test_update_S_infinite_and_nan_weights(ctx, n, events):
+    """An infinite weight makes an infinite residual whatever its code, and with it every target further
+    left infinite with the sign of the residual times L, so the choices there are the largest or the
+    lowest code; a NaN makes every target NaN, which takes the lowest code.  Q and the residuals that
+    later columns see agree, inside a block, a super-block and across them."""
+    m, nbits = 4 * len(events) + 3, 4
+    W, X = make_problem(m, n, 2 * n, nbits, seed=n)
+    L32 = torch.from_numpy(ref.cholesky(ref.build_hessian(X.numpy()))[0]).float()
+    L32 = torch.tril(torch.where(L32 == 0, 1e-6, L32))
+    T = torch.from_numpy(ref.init_codebooks(W.numpy(), nbits)).float()
+    T = T[:, torch.randperm(16, generator=torch.Generator().manual_seed(n))].contiguous()
+    lowest, largest = T.argmin(1), T.argmax(1)
+    clean = ctx.update_S(W.cuda(), L32.cuda(), T.cuda(), nbits).cpu()
+    want, Wx = clean.clone(), W.clone()
+    cases = [(j, v) for j in events for v in (float("inf"), float("-inf"), float("nan"))]
+    for i, (j, v) in enumerate(cases):
+        Wx[i, j] = v
+        want[i, j] = largest[i] if v > 0 else lowest[i]
+        up = (v * L32[j, :j]) > 0                     # NaN compares false
+        want[i, :j] = torch.where(up, largest[i], lowest[i]).to(torch.uint8)
+    Q, E = ctx.update_S(Wx.cuda(), L32.cuda(), T.cuda(), nbits, want_E=True)
+    Q, E = Q.cpu(), E.cpu()
+    assert torch.equal(Q, want)
+    Eref = Wx - torch.gather(T, 1, Q.long())
+    assert torch.equal(torch.nan_to_num(E, nan=7.0), torch.nan_to_num(Eref, nan=7.0))
