@@ -126,7 +126,9 @@ const char* ganq_last_error(const ganq_ctx* ctx);
  * the fp32 accumulator; fp32 input takes fp32 matrix-core products, nothing is
  * rounded down).  H is n x n fp32,
  * both triangles written.  accumulate != 0 adds to the H already there
- * (streaming token chunks).  Requires p % 8 == 0 and ldx % 8 == 0 for fp16. */
+ * (streaming token chunks).  Requires p % 8 == 0 and ldx % 8 == 0 for fp16.
+ * fp32 input cuts the tokens into up to 16 runs, as many as the workspace holds
+ * n x n partial sums for (one is enough; the runs differ in rounding only). */
 ganq_status ganq_build_hessian(ganq_ctx* ctx, const void* X, ganq_dtype x_dtype, int64_t n,
                                int64_t p, int64_t ldx, float* H, int64_t ldh, int accumulate);
 

@@ -1,6 +1,7 @@
 // Host side of the C ABI declared in ganq.h: argument checks, workspace
 // carving, and the order in which the gfx950 kernels are enqueued.  No
 // arithmetic of the method lives here.
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -122,6 +123,14 @@ Arena call_arena(ganq_ctx* ctx, size_t need) {
       ctx->tprep.valid = false;
   }
   return ar;
+}
+
+// Token splits of an fp32 H: as many as its size asks for, or as `room` bytes hold partial sums of (one
+// is always taken: whether it fits is checked where it is carved).
+int fit_f32_split(int64_t n, int64_t p, size_t room) {
+  int split = hessian_f32_split(n, p);
+  while (split > 1 && hessian_f32_scratch_bytes(n, split) > room) split /= 2;
+  return split;
 }
 
 // row losses -> host double; scratch = [E][F][row values][double]
@@ -303,13 +312,13 @@ size_t ganq_workspace_bytes(int64_t m, int64_t n, int64_t p_tokens, int nbits) {
   if (m > kMaxDim || n > kMaxDim || p_tokens > ((int64_t)1 << 40)) return 0;
   size_t q = quantize_scratch_bytes(m, n, nbits);
   size_t h = hessian_scratch_bytes(n, p_tokens > 0 ? p_tokens : 1) + kAlign;
-  size_t h32 = hessian_f32_scratch_bytes(n, p_tokens) + kAlign;
+  size_t h32 = align_up(hessian_f32_scratch_bytes(n, hessian_f32_split(n, p_tokens))) + kAlign;
   if (h32 > h) h = h32;
   if (p_tokens > 0) {     // token-major entry point: transposed chunk + the scratch of its product
     const int64_t p8 = (p_tokens + 7) / 8 * 8;
     const int64_t pc = p8 < kTokenChunk ? p8 : kTokenChunk;
     size_t hp = hessian_scratch_bytes(n, p8) + kAlign;
-    const size_t hp32 = hessian_f32_scratch_bytes(n, p8) + kAlign;
+    const size_t hp32 = align_up(hessian_f32_scratch_bytes(n, hessian_f32_split(n, p8))) + kAlign;
     if (hp32 > hp) hp = hp32;
     const size_t ht = align_up((size_t)n * pc * sizeof(float)) + hp + 4 * kAlign;
     if (ht > h) h = ht;
@@ -509,16 +518,16 @@ ganq_status ganq_build_hessian(ganq_ctx* ctx, const void* X, ganq_dtype x_dtype,
   if (st != GANQ_OK) return st;
   hipStream_t s = ctx->stream;
   Arena ar = call_arena(ctx, x_dtype == GANQ_F16 ? hessian_scratch_bytes(n, p > 0 ? p : 1)
-                                                 : hessian_f32_scratch_bytes(n, p));
+                                                 : hessian_f32_scratch_bytes(n, 1));
   ProfScope prof(ctx, GANQ_K_HESSIAN);
   if (x_dtype == GANQ_F16) {
     float* part = (float*)ar.take(hessian_scratch_bytes(n, p > 0 ? p : 1));
     if (part == nullptr) return fail(ctx, GANQ_ERR_WORKSPACE, "workspace too small for H = X X^T");
     GANQ_HIP(ctx, launch_hessian_f16(s, (const _Float16*)X, n, p, ldx, H, ldh, accumulate, part));
   } else {
-    float* tmp = (float*)ar.take(hessian_f32_scratch_bytes(n, p));
+    const int split = fit_f32_split(n, p, ar.room());
+    float* tmp = (float*)ar.take(hessian_f32_scratch_bytes(n, split));
     if (tmp == nullptr) return fail(ctx, GANQ_ERR_WORKSPACE, "workspace too small for H = X X^T");
-    const int split = hessian_f32_split(n, p);
     GANQ_HIP(ctx, launch_gemm_f32(s, 1, 1, n, n, p, 1.f, (const float*)X, ldx, (const float*)X, ldx,
                                   0.f, tmp, n, split, n * n));
     GANQ_HIP(ctx, launch_mirror_lower(s, H, n, ldh, tmp, split, accumulate));
@@ -556,8 +565,10 @@ ganq_status ganq_build_hessian_tokens(ganq_ctx* ctx, const void* Xt, ganq_dtype 
   // fewer, larger products).
   ctx->tprep.valid = false;          // this call sizes its chunks by the whole workspace
   const int64_t p8 = (p + 7) / 8 * 8;
-  const size_t part_bytes = (x_dtype == GANQ_F16) ? hessian_scratch_bytes(n, p8) : hessian_f32_scratch_bytes(n, p8);
   int64_t chunk = p8 < kTokenChunk ? p8 : kTokenChunk;
+  const size_t xn_bytes = align_up((size_t)n * chunk * eb);
+  const int max_split = fit_f32_split(n, p8, ctx->ws_bytes > xn_bytes ? ctx->ws_bytes - xn_bytes : 0);
+  const size_t part_bytes = (x_dtype == GANQ_F16) ? hessian_scratch_bytes(n, p8) : hessian_f32_scratch_bytes(n, max_split);
   if (ctx->ws_bytes > part_bytes + 4 * kAlign) {
     const int64_t fit = (int64_t)((ctx->ws_bytes - part_bytes - 4 * kAlign) / ((size_t)n * eb)) / 2048 * 2048;
     if (fit > chunk) chunk = fit < p8 ? fit : p8;
@@ -581,7 +592,7 @@ ganq_status ganq_build_hessian_tokens(ganq_ctx* ctx, const void* Xt, ganq_dtype 
     if (x_dtype == GANQ_F16) {
       GANQ_HIP(ctx, launch_hessian_f16(s, (const _Float16*)Xn, n, pc8, pc8, H, ldh, acc, part));
     } else {
-      const int split = hessian_f32_split(n, pc8);
+      const int split = std::min(hessian_f32_split(n, pc8), max_split);
       GANQ_HIP(ctx, launch_gemm_f32(s, 1, 1, n, n, pc8, 1.f, (const float*)Xn, pc8, (const float*)Xn, pc8,
                                     0.f, part, n, split, n * n));
       GANQ_HIP(ctx, launch_mirror_lower(s, H, n, ldh, part, split, acc));

@@ -107,6 +107,10 @@ struct Arena {
     off = a + bytes;
     return base + a;
   }
+  size_t room() const {
+    const size_t a = align_up(off);
+    return a < cap ? cap - a : 0;
+  }
 };
 
 // ---- sizes of scratch regions (shared by ganq_workspace_bytes and the calls) ----
@@ -117,7 +121,7 @@ constexpr int kHessMaxSplit = 16;   // upper bound on token-axis splits
 int hessian_split(int64_t n, int64_t p);
 size_t hessian_scratch_bytes(int64_t n, int64_t p);
 int hessian_f32_split(int64_t n, int64_t p);
-size_t hessian_f32_scratch_bytes(int64_t n, int64_t p);
+size_t hessian_f32_scratch_bytes(int64_t n, int split);
 constexpr int64_t kTokenChunk = 32768;   // tokens transposed at a time by the token-major entry point
 bool hessian_tokens_direct_ok(const void* Xt, int64_t n, int64_t p, int64_t ldxt);
 hipError_t launch_hessian_f16_tokens(hipStream_t s, const _Float16* Xt, int64_t n, int64_t p, int64_t ldxt,

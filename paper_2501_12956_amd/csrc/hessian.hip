@@ -361,8 +361,8 @@ int hessian_f32_split(int64_t n, int64_t p) {
   return split;
 }
 
-size_t hessian_f32_scratch_bytes(int64_t n, int64_t p) {
-  return align_up((size_t)hessian_f32_split(n, p) * (size_t)n * (size_t)n * sizeof(float));
+size_t hessian_f32_scratch_bytes(int64_t n, int split) {
+  return (size_t)split * (size_t)n * (size_t)n * sizeof(float);
 }
 
 // Requires p % 8 == 0, ldx % 8 == 0, ldx < 2^22 and a 16-byte aligned X (checked by the caller).

@@ -1063,3 +1063,54 @@ def test_update_S_infinite_and_nan_weights(ctx, n, events):
     assert torch.equal(Q, want)
     Eref = Wx - torch.gather(T, 1, Q.long())
     assert torch.equal(torch.nan_to_num(E, nan=7.0), torch.nan_to_num(Eref, nan=7.0))
+
+
+def _raw_context(nbytes):
+    """A context with exactly this much workspace (the binding's own grows on demand)."""
+    from paper_2501_12956_amd import binding as b
+    c = b.Context(0)
+    ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+    assert c.lib.ganq_set_workspace(c.handle, ws.data_ptr(), nbytes) == b.GANQ_OK
+    return c, ws
+
+
+def test_hessian_fp32_takes_the_splits_its_workspace_holds():
+    """One matrix of partial sums is enough for any number of tokens; fewer bytes are refused.  Prepared
+    T-update inputs stay while one fits behind them."""
+    from paper_2501_12956_amd import binding as b
+    n, p = 200, 4099
+    g = torch.Generator().manual_seed(1)
+    X = torch.randn(n, p, generator=g)
+    Href = ref.build_hessian(X.numpy())
+    Xg, Xt = X.cuda(), X.t().contiguous().cuda()
+    one, xn = 4 * n * n, 4 * n * ((p + 7) // 8 * 8)
+    for nbytes in (one, 2 * one, 5 * one, 16 * one):
+        c, ws = _raw_context(nbytes)
+        H = torch.empty(n, n, device="cuda")
+        assert c.lib.ganq_build_hessian(c.handle, Xg.data_ptr(), 1, n, p, p, H.data_ptr(), n, 0) == b.GANQ_OK
+        check_H(H.cpu().numpy().astype(np.float64), Href, p, wide=True)
+        c.close()
+        c, ws = _raw_context(nbytes + (xn + 255) // 256 * 256)
+        H2 = torch.empty(n, n, device="cuda")
+        assert c.lib.ganq_build_hessian_tokens(c.handle, Xt.data_ptr(), 1, n, p, n, H2.data_ptr(), n, 0) == b.GANQ_OK
+        check_H(H2.cpu().numpy().astype(np.float64), Href, p, wide=True)
+        c.close()
+    c, ws = _raw_context(one - 256)
+    assert c.lib.ganq_build_hessian(c.handle, Xg.data_ptr(), 1, n, p, p, H.data_ptr(), n, 0) == b.GANQ_ERR_WORKSPACE
+    c.close()
+
+    m, n, nbits = 64, 640, 4
+    g = torch.Generator().manual_seed(2)
+    W, X = torch.randn(m, n, generator=g).cuda(), torch.randn(n, 4096, generator=g).cuda()
+    H = X @ X.t()
+    Q = torch.randint(0, 16, (m, n), generator=g, dtype=torch.uint8).cuda()
+    T, H2 = torch.zeros(m, 16, device="cuda"), torch.empty(n, n, device="cuda")
+    c, ws = _raw_context(b.load_library().ganq_workspace_bytes(m, n, 0, nbits))
+    assert c.lib.ganq_update_T_prepare(c.handle, W.data_ptr(), m, n, n, H.data_ptr(), n, nbits) == b.GANQ_OK
+    c.profile_enable(True)
+    assert c.lib.ganq_build_hessian(c.handle, X.data_ptr(), 1, n, 4096, 4096, H2.data_ptr(), n, 0) == b.GANQ_OK
+    assert c.lib.ganq_update_T(c.handle, W.data_ptr(), m, n, n, H.data_ptr(), n, Q.data_ptr(), n, nbits, 0, T.data_ptr(),
+                               None) == b.GANQ_OK
+    prof = c.profile_read()
+    assert prof["gemm_wh"][1] == 0 and prof["t_prep"][1] == 0
+    c.close()
