@@ -103,8 +103,8 @@ size_t quantize_scratch_bytes(int64_t m, int64_t n, int nbits) {
   b += align_up((size_t)m * n * sizeof(float));        // W in fp32
   b += align_up((size_t)n * own_ldl(n) * sizeof(float));   // L
   b += align_up((size_t)m * n * sizeof(float));        // G = W H
-  b += cholesky_scratch_bytes(n);
-  b += update_s_scratch_bytes(m, n);
+  // one after the other in the same place
+  b += std::max(align_up(cholesky_scratch_bytes(n)), m > 0 ? align_up(update_s_scratch_bytes(m, n)) : 0);
   b += update_t_scratch_bytes(m, n, nbits);
   b += loss_scratch_bytes(m, n);
   b += outlier_scratch_bytes(m);
@@ -829,7 +829,7 @@ ganq_status ganq_quantize_layer(ganq_ctx* ctx, const void* W, ganq_dtype w_dtype
 
   // all scratch is carved before the first launch: with the factorisation done here, the work
   // that does not need L (conversion of W, T^0, G = W H, the split of H) runs on a second stream
-  // beside it, so none of these buffers may share space with the factorisation's scratch
+  // beside it, so none of the buffers of that work may share space with the factorisation's scratch
   float* Wbuf = nullptr;
   if (w_dtype == GANQ_F16) {
     Wbuf = (float*)ar.take((size_t)m * n * sizeof(float));
@@ -841,9 +841,12 @@ ganq_status ganq_quantize_layer(ganq_ctx* ctx, const void* W, ganq_dtype w_dtype
     if (Lbuf == nullptr) return fail(ctx, GANQ_ERR_WORKSPACE, "workspace too small (L)");
   }
   float* G = (float*)ar.take((size_t)m * n * sizeof(float));
-  void* s_scratch = ar.take(update_s_scratch_bytes(m, n));
   void* t_scratch = ar.take(update_t_scratch_bytes(m, n, nbits));
   void* gs = ar.take(gemm_split_scratch_bytes(m, n, n));
+  // the S-update begins when the factorisation and the work beside it are done, so its scratch (pieces
+  // of L and of the residuals) takes the place of the factorisation's working copy
+  Arena chol(ar);
+  void* s_scratch = ar.take(update_s_scratch_bytes(m, n));
   if (G == nullptr || s_scratch == nullptr || t_scratch == nullptr || gs == nullptr)
     return fail(ctx, GANQ_ERR_WORKSPACE, "workspace too small (solver scratch)");
 
@@ -892,8 +895,7 @@ ganq_status ganq_quantize_layer(ganq_ctx* ctx, const void* W, ganq_dtype w_dtype
   if (forked) {
     if (pe == hipSuccess) pe = hipEventRecord(ctx->join_ev, pre);
     int64_t info = 0;
-    Arena sub((char*)ctx->ws + align_up(ar.off), ctx->ws_bytes - align_up(ar.off));
-    st = run_cholesky(ctx, sub, H, n, ldh, o.precond, o.lambda, Lbuf, own_ldl(n), &info);
+    st = run_cholesky(ctx, chol, H, n, ldh, o.precond, o.lambda, Lbuf, own_ldl(n), &info);
     if (st != GANQ_OK || pe != hipSuccess) {
       hipStreamSynchronize(pre);     // nothing of this call may still run when it returns
       if (st != GANQ_OK) return st;

@@ -62,6 +62,14 @@ def test_workspace_query(lib):
     assert big < 8 * (1 << 30)
 
 
+def test_workspace_of_large_layers(lib):
+    """Four matrices of H's size are what a layer needs at once (the factor, its working copy or the pieces
+    of it, the digits of H, the pieces of H) and nine of W's, plus what grows with one dimension only."""
+    for m, n in ((0, 28672), (0, 11008), (8192, 28672), (4096, 11008)):
+        hh, ww = 4 * n * n, 4 * m * n
+        assert lib.ganq_workspace_bytes(m, n, 0, 4) <= 4.1 * hh + 9.0 * ww + 2 ** 28
+
+
 def test_argument_checks_run_on_the_host(lib):
     from paper_2501_12956_amd import binding as b
     h = ctypes.c_void_p()

@@ -1114,3 +1114,20 @@ def test_hessian_fp32_takes_the_splits_its_workspace_holds():
     prof = c.profile_read()
     assert prof["gemm_wh"][1] == 0 and prof["t_prep"][1] == 0
     c.close()
+
+
+@pytest.mark.parametrize("m,n,nbits,given_L", [(40, 200, 4, False), (33, 1100, 3, False), (70, 2100, 4, False), (300, 1300, 2, True)])
+def test_quantize_layer_in_exactly_the_workspace_it_asks_for(ctx, m, n, nbits, given_L):
+    """The buffers that share space inside the call (factorization, S-update) do not change its results."""
+    from paper_2501_12956_amd import binding as b
+    W, X = make_problem(m, n, 2 * n, nbits, seed=n)
+    Wg, H = W.half().cuda(), dev(ref.build_hessian(X.numpy()), torch.float32)
+    L = ctx.cholesky(H)[0] if given_L else None
+    ctx.reserve(m, n, 0, nbits, extra=1 << 28)
+    want = ctx.quantize_layer(Wg, H, nbits, 3, L=L, history=True)
+    c, ws = _raw_context(b.load_library().ganq_workspace_bytes(m, n, 0, nbits))
+    c._ws = ws                                   # large enough by the library's own answer: never replaced
+    got = c.quantize_layer(Wg, H, nbits, 3, L=L, history=True)
+    assert c._ws is ws
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]) and np.array_equal(got[2], want[2])
+    c.close()
