@@ -116,9 +116,12 @@ struct FieldOffsets {
 };
 
 // SW = segment lanes (1, 2, 4 or 8 wavefronts side by side on one row); the other
-// 8 / SW wavefronts take different rows, so every wavefront owns 2 SW of the 16 rows.
-template <int N, int SW>
-__global__ __launch_bounds__(64 * GNW, 4) void lut_gemv_kernel(
+// 8 / SW wavefronts take different rows, so every wavefront owns 2 SW of the 16 rows.  SPARSE: with
+// outliers (a kernel of its own: what they hold in registers costs a workgroup per compute unit).
+// At most 80 scalar registers, with the 16 that the trap handler holds still eight wavefronts per SIMD:
+// 13824 x 5120 at 3 bits with outliers 18.1 -> 16.5 us.
+template <int N, int SW, bool SPARSE>
+__global__ __launch_bounds__(64 * GNW, 4) __attribute__((amdgpu_num_sgpr(80))) void lut_gemv_kernel(
     const uint8_t* __restrict__ packed, int64_t ldp, const uint16_t* __restrict__ lut, int64_t m,
     int64_t n, const _Float16* __restrict__ x, float* __restrict__ y,
     const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
@@ -134,7 +137,7 @@ __global__ __launch_bounds__(64 * GNW, 4) void lut_gemv_kernel(
   constexpr int TW = 1 << F;                   // table words per row
   constexpr int LPG = 32 * N / F;              // look-ups per 32-code group
   __shared__ __attribute__((aligned(16))) uint32_t tab[GR][TW];
-  __shared__ float part[SW][GR], spart[GR];
+  __shared__ float part[SW][GR], spart[SPARSE && SW > 1 ? GR : 1];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -177,29 +180,28 @@ __global__ __launch_bounds__(64 * GNW, 4) void lut_gemv_kernel(
       for (int w = 0; w < N; ++w) q[k][w] = ok ? q[k][w] : 0u;
     }
   };
-  // At 4 bits the first segment is requested before the tables are built: with few segments per
-  // wavefront there is little else to hide its latency behind (8192 x 8192 with outliers 18.1 -> 14.8 us a layer).  At
-  // 3 bits and less the rows are short enough that the longer code costs more than it hides (28 layers
-  // 217 -> 227 us), and 16 rows of 4-bit groups leave no registers to wait in.
-  constexpr bool AHEAD = N == 4 && RPW < 16;
+  // At 4 bits and eight rows a wavefront the first segment is requested before the tables are built: each
+  // has one or few, and little else to hide their latency behind (28672 x 8192 40.1 -> 35.5 us, with
+  // outliers 58 -> 43).  With fewer rows the registers cost a workgroup per compute unit (11008 x 4096 10.4
+  // -> 11.9 us), at 3 bits and less the longer code costs more than it hides, and with sixteen rows there
+  // are no registers to wait in.
+  constexpr bool AHEAD = N == 4 && SW == 4;
   uint32_t xr[16], q[RPW][N];
   if (AHEAD && sl < nseg) {
     load_x(sl, xr);
     load_q(sl, q);
   }
-  // outliers: every wavefront takes two of the 16 rows, 64 entries at a time
-  int64_t oe[2], oend[2];
+  // outliers: every wavefront takes two of the 16 rows, 64 entries at a time; its own two where it has two
+  constexpr bool OWN = SW == 1;
+  int64_t ob[2], on[2];           // a row's first entry and their number, the same in every lane
   int32_t oc[2];
   float ov[2];
-  if (row_ptr != nullptr) {
+  if constexpr (SPARSE) {
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
-      const int64_t row = row0 + 2 * wave + k;
-      oe[k] = (row < m) ? row_ptr[row] + lane : 0;
-      oend[k] = (row < m) ? row_ptr[row + 1] : 0;
-      const bool ok = oe[k] < oend[k];
-      oc[k] = ok ? col_idx[oe[k]] : 0;
-      ov[k] = ok ? values[oe[k]] : 0.f;
+      const int64_t row = row0 + (OWN ? g + RG * k : 2 * wave + k);
+      ob[k] = (row < m) ? row_ptr[row] : 0;
+      on[k] = (row < m) ? row_ptr[row + 1] - ob[k] : 0;
     }
   }
 
@@ -215,6 +217,16 @@ __global__ __launch_bounds__(64 * GNW, 4) void lut_gemv_kernel(
   }
   const uint32_t gbase = (uint32_t)g * (TW * 4u);   // this wavefront's rows are g, g + RG, ...
   __syncthreads();
+  // the entries themselves are requested behind the tables: in front of them their two dependent reads
+  // hold up every wavefront of the workgroup
+  if constexpr (SPARSE) {
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const bool ok = lane < on[k];
+      oc[k] = ok ? col_idx[ob[k] + lane] : 0;
+      ov[k] = ok ? values[ob[k] + lane] : 0.f;
+    }
+  }
 
   float acc[RPW];
 #pragma unroll
@@ -278,16 +290,20 @@ __global__ __launch_bounds__(64 * GNW, 4) void lut_gemv_kernel(
     }
   }
 
-  if (row_ptr != nullptr) {
+  if constexpr (SPARSE) {
     const uint16_t* xs = reinterpret_cast<const uint16_t*>(x);
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
       float a = 0.f;
-      if (oe[k] < oend[k]) a = ov[k] * (float)__builtin_bit_cast(_Float16, xs[oc[k]]);
-      for (int64_t e = oe[k] + 64; e < oend[k]; e += 64)
-        a = fmaf(values[e], (float)__builtin_bit_cast(_Float16, xs[col_idx[e]]), a);
-      a = wave_sum63(a);
-      if (lane == 63) spart[2 * wave + k] = a;
+      if (lane < on[k]) a = ov[k] * (float)__builtin_bit_cast(_Float16, xs[oc[k]]);
+      for (int64_t e = lane + 64; e < on[k]; e += 64)
+        a = fmaf(values[ob[k] + e], (float)__builtin_bit_cast(_Float16, xs[col_idx[ob[k] + e]]), a);
+      if constexpr (OWN) {
+        acc[k] += a;
+      } else {
+        a = wave_sum63(a);
+        if (lane == 63) spart[2 * wave + k] = a;
+      }
     }
   }
 
@@ -301,7 +317,7 @@ __global__ __launch_bounds__(64 * GNW, 4) void lut_gemv_kernel(
     float v = part[0][tid];
 #pragma unroll
     for (int s2 = 1; s2 < SW; ++s2) v += part[s2][tid];
-    if (row_ptr != nullptr) v += spart[tid];
+    if constexpr (SPARSE && !OWN) v += spart[tid];
     y[row0 + tid] = v;
   }
 }
@@ -369,18 +385,16 @@ hipError_t launch_gemv_n(hipStream_t s, const uint8_t* packed, int64_t ldp, cons
     const int64_t slots = ceil_div(nseg, c) * c;
     if (slots <= best) { best = slots; sw = c; }
   }
-  if (sw == 8)
-    hipLaunchKernelGGL((lut_gemv_kernel<N, 8>), grid, block, 0, s, packed, ldp, lut, m, n, x, y, row_ptr,
-                       col_idx, values);
-  else if (sw == 4)
-    hipLaunchKernelGGL((lut_gemv_kernel<N, 4>), grid, block, 0, s, packed, ldp, lut, m, n, x, y, row_ptr,
-                       col_idx, values);
-  else if (sw == 2)
-    hipLaunchKernelGGL((lut_gemv_kernel<N, 2>), grid, block, 0, s, packed, ldp, lut, m, n, x, y, row_ptr,
-                       col_idx, values);
-  else
-    hipLaunchKernelGGL((lut_gemv_kernel<N, 1>), grid, block, 0, s, packed, ldp, lut, m, n, x, y, row_ptr,
-                       col_idx, values);
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, block, 0, s, packed, ldp, lut, m, n, x, y, row_ptr, col_idx, values);
+  };
+  const bool sp = row_ptr != nullptr;
+  switch (sw) {
+    case 8: launch(sp ? lut_gemv_kernel<N, 8, true> : lut_gemv_kernel<N, 8, false>); break;
+    case 4: launch(sp ? lut_gemv_kernel<N, 4, true> : lut_gemv_kernel<N, 4, false>); break;
+    case 2: launch(sp ? lut_gemv_kernel<N, 2, true> : lut_gemv_kernel<N, 2, false>); break;
+    default: launch(sp ? lut_gemv_kernel<N, 1, true> : lut_gemv_kernel<N, 1, false>); break;
+  }
   return hipGetLastError();
 }
 

@@ -164,3 +164,24 @@ def test_lut_gemv_strided_storage_unaligned_x_and_empty_outlier_rows(ctx):
     check_product(y.cpu().numpy().astype(np.float64), lut.cpu().numpy(), Q, x, Ws.astype(np.float64))
     y0 = ctx.lut_gemv(packed, lut, nbits, n, torch.from_numpy(x).cuda(), outliers=(row_ptr, col, val))
     assert torch.equal(y, y0)
+
+
+@pytest.mark.parametrize("nbits", [1, 2, 3, 4])
+@pytest.mark.parametrize("n", [1500, 4000, 8000, 16000])
+def test_lut_gemv_outliers_in_every_arrangement(ctx, n, nbits):
+    """One, two, four and eight wavefronts side by side on a row, each with rows of no outlier, one, and up
+    to, exactly and more than one wavefront's width of them; a last workgroup that is not full."""
+    m = 35
+    T, Q, x = random_layer(m, n, nbits, n + nbits)
+    packed, lut = ctx.pack_layer(torch.from_numpy(Q).cuda(), torch.from_numpy(T).cuda(), nbits)
+    rng = np.random.default_rng(n)
+    Ws = np.zeros((m, n), dtype=np.float32)
+    for i in range(m):
+        k = (0, 1, 63, 64, 65, 300)[i % 6]
+        Ws[i, rng.choice(n, size=k, replace=False)] = rng.standard_normal(k)
+    nz = [np.flatnonzero(Ws[i]) for i in range(m)]
+    row_ptr = torch.tensor(np.concatenate([[0], np.cumsum([len(c) for c in nz])]), dtype=torch.int64).cuda()
+    col = torch.tensor(np.concatenate(nz), dtype=torch.int32).cuda()
+    val = torch.tensor(np.concatenate([Ws[i, c] for i, c in enumerate(nz)]), dtype=torch.float32).cuda()
+    y = ctx.lut_gemv(packed, lut, nbits, n, torch.from_numpy(x).cuda(), outliers=(row_ptr, col, val))
+    check_product(y.cpu().numpy().astype(np.float64), lut.cpu().numpy(), Q, x, Ws.astype(np.float64))
