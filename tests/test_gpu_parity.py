@@ -1131,3 +1131,38 @@ def test_quantize_layer_in_exactly_the_workspace_it_asks_for(ctx, m, n, nbits, g
     assert c._ws is ws
     assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]) and np.array_equal(got[2], want[2])
     c.close()
+
+
+@pytest.mark.parametrize("dtype", [torch.float16, torch.float32])
+@pytest.mark.parametrize("m,n", [(1, 1), (3, 2), (4, 17), (5, 63), (9, 64), (6, 65)])
+def test_init_codebooks_of_short_rows(ctx, m, n, dtype):
+    """Rows of at most 64 elements are ranked by comparing all pairs: ties, both zeros, an infinite
+    largest element, rows off a 16-byte boundary, a last workgroup that is not full."""
+    from paper_2501_12956_amd import binding as b
+    g = torch.Generator().manual_seed(100 * m + n)
+    W = torch.randn(m, n, generator=g)
+    W[m // 2] = torch.randint(0, 3, (n,), generator=g).float()
+    W[m // 2, : n // 3] = -0.0
+    W = W.to(dtype)
+    wide = torch.zeros(m, n + 3, dtype=dtype, device="cuda")
+    wide[:, 1:n + 1].copy_(W)
+    for nbits in (1, 3, 4):
+        for mode, omode in [(b.INIT_QUANTILE_MID, ref.INIT_QUANTILE_MID),
+                            (b.INIT_QUANTILE_ENDPOINTS, ref.INIT_QUANTILE_ENDPOINTS),
+                            (b.INIT_MINMAX_GRID, ref.INIT_MINMAX_GRID)]:
+            Tref = ref.init_codebooks(W.float().numpy(), nbits, omode)
+            ulp = np.spacing(np.abs(Tref).astype(np.float32)).astype(np.float64)
+            for Wg in (W.cuda(), wide[:, 1:n + 1]):
+                T = ctx.init_codebooks(Wg, nbits, mode).cpu().numpy()
+                assert np.all(np.abs(T.astype(np.float64) - Tref) <= ulp)
+    # the largest of a row may be infinite: below it nothing changes
+    if n >= 17:
+        Wi = W.clone()
+        Wi[:, 0] = float("inf")
+        T = ctx.init_codebooks(Wi.cuda(), 4).cpu().numpy()
+        rest = np.sort(Wi.float().numpy().astype(np.float64), axis=1)
+        h = (np.arange(16) + 0.5) / 16 * (n - 1)
+        lo = np.floor(h).astype(int)
+        keep = lo + 1 < n - 1
+        want = rest[:, lo[keep]] + (h - lo)[keep] * (rest[:, lo[keep] + 1] - rest[:, lo[keep]])
+        assert np.all(np.abs(T[:, keep] - want) <= np.spacing(np.abs(want).astype(np.float32)))
