@@ -61,7 +61,7 @@ struct BlockArgs {
   _Float16* Ep;              // residual pieces of the whole layer
   const _Float16* LF;        // pieces of L inside the super-blocks, in the order of the sweep's loads
   int64_t kp;                // rows of Ep hold 2 kp halves
-  const float* wmax;         // max |W_i|
+  const float* wmax;         // max |W_i|; null where no residual is ever multiplied as pieces
   int* ea;                   // exponents of the rows of Ep, written by the first super-block
   const int* eb;             // exponents of the columns of L
 };
@@ -252,7 +252,7 @@ __global__ __launch_bounds__(64 * NW) void update_S_kernel(const float* __restri
     tm = fmaxf(tm, dpp_f<0x4E>(tm));
     tm = fmaxf(tm, dpp_f<0x141>(tm));
     tm = fmaxf(tm, dpp_f<0x140>(tm));
-    tm += row_ok ? sb.wmax[row] : 0.f;
+    tm += (row_ok && sb.wmax != nullptr) ? sb.wmax[row] : 0.f;
     const int ea = (tm > 0.f && tm < __builtin_huge_valf()) ? 14 - ilogbf(tm) : 0;
     if (c == 0) {
       eal[r] = ea;
@@ -630,8 +630,10 @@ hipError_t launch_update_S_prepare(hipStream_t s, const float* W, int64_t m, int
                                    int64_t ldl, void* scratch) {
   const SScratch sc(scratch, m, n);
   hipError_t e;
-  hipLaunchKernelGGL(s_rowmax_kernel, dim3((unsigned)m), dim3(256), 0, s, W, n, ldw, sc.wmax);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
+  if (n > 2 * SB) {
+    hipLaunchKernelGGL(s_rowmax_kernel, dim3((unsigned)m), dim3(256), 0, s, W, n, ldw, sc.wmax);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
   const unsigned c64 = (unsigned)ceil_div(n, 64);
   hipLaunchKernelGGL(l_column_kernel, dim3(c64), dim3(1024), 0, s, L, n, ldl, sc.rdiag, sc.eb);
   if ((e = hipGetLastError()) != hipSuccess || c64 < 2) return e;
@@ -661,7 +663,7 @@ hipError_t launch_update_S(hipStream_t s, const float* W, int64_t m, int64_t n, 
     sb.Ep = sc.Ep;
     sb.LF = sc.LF;
     sb.kp = kp;
-    sb.wmax = sc.wmax;
+    sb.wmax = (n > 2 * SB) ? sc.wmax : nullptr;     // a block and the one after it update each other in fp32
     sb.ea = sc.ea;
     sb.eb = sc.eb;
     if (sb.jhi < n) {
