@@ -81,3 +81,100 @@ def test_cholesky_pivots_are_not_biased(ctx):
         bias = ((torch.tril(L).double().square().sum(1) - d) / d).mean().item()
         print("mean of (L L^T - H)_jj / H_jj: %.2e" % bias)
         assert abs(bias) <= 7e-9
+
+
+@pytest.mark.parametrize("n,p", [(4480, 4400), (4500, 4490), (8192, 8000)])
+def test_cholesky_reports_a_singular_matrix_beyond_the_split_update(ctx, n, p):
+    """Fewer tokens than features where the first trailing updates are split products: the pivots from p on
+    are rounding noise (those right before it hardly more), and one of the first must be reported; AUTO
+    then factors the preconditioned matrix."""
+    from paper_2501_12956_amd import binding as b
+    H = _gram(n, p, n)
+    _, info = ctx.cholesky(H, b.PRECOND_NONE, raise_on_fail=False)
+    assert p - 8 < info <= p + 8, info
+    L, info = ctx.cholesky(H, b.PRECOND_AUTO)
+    assert info == 0
+    Hd = H.double()
+    delta = (Hd.abs().sum(1) - 2 * torch.diagonal(Hd)).clamp(min=1e-8)
+    Hp = Hd + torch.diag(delta)
+    R = torch.tril(L).double() @ torch.tril(L).double().t() - Hp
+    assert R.norm().item() <= 2e-6 * Hp.norm().item()
+
+
+@pytest.mark.parametrize("where", ["column", "diagonal", "nan"])
+def test_cholesky_reports_the_first_bad_pivot_beyond_the_split_update(ctx, where):
+    """Not finite below the first panel, or an exact copy of a feature: the pivot of that row is the first
+    that fails, as it is in smaller matrices."""
+    from paper_2501_12956_amd import binding as b
+    n, k = 4500, 4321
+    g = torch.Generator(device="cuda").manual_seed(3)
+    X = torch.randn(n, 2 * n, generator=g, device="cuda").double()
+    if where == "column":
+        X[k] = X[17]
+    H = (X @ X.t()).float()
+    if where == "diagonal":
+        H[k, 40] = H[40, k] = float("inf")
+    if where == "nan":
+        H[k, 4300] = H[4300, k] = float("nan")
+    _, info = ctx.cholesky(H, b.PRECOND_NONE, raise_on_fail=False)
+    assert info == k + 1
+
+
+def test_large_tiles_with_remainders_in_every_direction(ctx):
+    """G = W H and F = E H take 256 x 256 tiles from 192 of them on; here 15 x 15 with 17 rows and 29
+    columns in the last ones and a last step of 29 columns.  Row losses against float64, and the codebooks
+    of the prepared T-update on the rows around the last tile's edge."""
+    m, n, nbits = 3601, 3613, 3
+    g = torch.Generator(device="cuda").manual_seed(4)
+    H = _gram(n, 2 * n, 5)
+    W = torch.randn(m, n, generator=g, device="cuda") * 0.02
+    W[torch.rand(m, n, generator=g, device="cuda") < 0.003] *= 10
+    T = ctx.init_codebooks(W, nbits)
+    Q = torch.empty(m, n, dtype=torch.uint8, device="cuda")
+    for r in range(0, m, 256):
+        Q[r:r + 256] = (W[r:r + 256, :, None] - T[r:r + 256, None, :]).abs().argmin(2).to(torch.uint8)
+    total, rows = ctx.layer_loss(W, H, T, Q, nbits, want_rows=True)
+    E = (W - torch.gather(T, 1, Q.long())).double()
+    want = ((E @ H.double()) * E).sum(1)
+    rel = ((rows.double() - want) / want).abs()
+    print("row losses: rms %.2e, max %.2e" % (rel.square().mean().sqrt().item(), rel.max().item()))
+    # about sqrt(3 n / 16) roundings of 2^-24 in a product's chain, summed over a row with random signs
+    assert rel.max().item() <= 5e-6 and abs(total - want.sum().item()) <= 1e-6 * want.sum().item()
+    T2 = T.clone()
+    ctx.update_T_prepare(W, H, nbits)
+    ctx.update_T(W, H, Q, T2, nbits)
+    ctx.update_T_prepare(None, None, nbits)
+    C = 1 << nbits
+    for i in list(range(0, 8)) + list(range(3580, 3601)):
+        S = torch.nn.functional.one_hot(Q[i].long(), C).double()
+        used = S.sum(0) > 0
+        A = (S.t() @ (H.double() @ S))[used][:, used]
+        t = torch.linalg.solve(A, ((W[i].double() @ H.double()) @ S)[used])
+        err = (T2[i].double()[used] - t).abs().max().item() / t.abs().max().item()
+        assert err <= 1e-4, (i, err)
+
+
+def _synthetic_factor(n, seed):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    L = torch.randn(n, n, generator=g, device="cuda").tril_(-1) * (0.3 / n ** 0.5)
+    L.diagonal().copy_(0.5 + torch.rand(n, generator=g, device="cuda"))
+    return L
+
+
+@pytest.mark.parametrize("m,n,nbits", [(5900, 2113, 4), (4097, 3203, 3), (133, 10411, 4), (4225, 5003, 2)])
+def test_update_S_choices_with_remainders_in_every_direction(ctx, m, n, nbits):
+    """One and two k-splits, rows, columns and steps that fill no tile: every choice on rows around the
+    tiles' edges is the nearest code of its float64 target, or a near tie."""
+    L = _synthetic_factor(n, n)
+    W = torch.randn(m, n, generator=torch.Generator(device="cuda").manual_seed(m), device="cuda") * 0.02
+    T = ctx.init_codebooks(W, nbits)
+    Q = ctx.update_S(W, L, T, nbits)
+    rows = sorted({r for e in range(0, m + 1, 128) for r in (e - 1, e) if 0 <= r < m} | {m - 1})
+    Wd, Td, Qr = W[rows].double(), T[rows].double(), Q[rows].long()
+    chosen = torch.gather(Td, 1, Qr)
+    Ld = L.double()
+    tgt = Wd + ((Wd - chosen) @ torch.tril(Ld, -1)) / torch.diagonal(Ld)
+    gap = (tgt - chosen).abs()
+    best = torch.stack([(tgt - Td[:, s:s + 1]).abs() for s in range(1 << nbits)]).amin(0)
+    rel = (gap - best) / Td.abs().amax(1, keepdim=True)
+    assert rel.max().item() < 1e-6
