@@ -145,9 +145,61 @@ __global__ __launch_bounds__(64 * GNW, 4) __attribute__((amdgpu_num_sgpr(80))) v
   const int64_t row0 = (int64_t)blockIdx.x * GR;
 
   const int64_t nseg = ceil_div(n, GSEG);
-  // this lane's 32 activations as 16 fp16 pairs; columns >= n count as zero
-  auto load_x = [&](int64_t seg, uint32_t (&xr)[16]) {
+  // At 4 bits and eight rows a wavefront the tables are built under the loads of its first segment: it has
+  // one or few, and little else to hide their latency behind (28672 x 8192 40.1 -> 33.3 us, with outliers
+  // 58 -> 42).  With fewer rows the registers cost a workgroup per compute unit (11008 x 4096 10.4 -> 11.9
+  // us), at 3 bits and less the longer code costs more than it hides, and with sixteen rows there are no
+  // registers to wait in.  Four segment lanes are taken only for whole multiples of four segments, so every
+  // wavefront enters the loop and meets the barrier in it.
+  constexpr bool AHEAD = N == 4 && SW == 4;
+  // outliers: every wavefront takes two of the 16 rows, 64 entries at a time; its own two where it has two
+  constexpr bool OWN = SW == 1;
+  int64_t ob[2], on[2];           // a row's first entry and their number, the same in every lane
+  int32_t oc[2];
+  float ov[2];
+  if constexpr (SPARSE) {
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int64_t row = row0 + (OWN ? g + RG * k : 2 * wave + k);
+      ob[k] = (row < m) ? row_ptr[row] : 0;
+      on[k] = (row < m) ? row_ptr[row + 1] - ob[k] : 0;
+    }
+  }
+
+  // the 16 rows' tables
+  auto tables = [&]() {
+    for (int e = tid; e < GR * TW; e += 64 * GNW) {
+      const int r = e / TW, idx = e % TW;
+      uint32_t v = 0u;
+      if (row0 + r < m) {
+        const uint16_t* lr = lut + (row0 + r) * C;
+        v = PAIR ? ((uint32_t)lr[idx & (C - 1)] | ((uint32_t)lr[idx >> N] << 16)) : (uint32_t)lr[idx];
+      }
+      tab[r][idx] = v;
+    }
+    __syncthreads();
+    // the outliers themselves are requested behind the tables: in front of them their two dependent reads
+    // hold up every wavefront of the workgroup
+    if constexpr (SPARSE) {
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const bool ok = lane < on[k];
+        oc[k] = ok ? col_idx[ob[k] + lane] : 0;
+        ov[k] = ok ? values[ob[k] + lane] : 0.f;
+      }
+    }
+  };
+  const uint32_t gbase = (uint32_t)g * (TW * 4u);   // this wavefront's rows are g, g + RG, ...
+  if constexpr (!AHEAD) tables();
+
+  float acc[RPW];
+#pragma unroll
+  for (int k = 0; k < RPW; ++k) acc[k] = 0.f;
+
+  for (int64_t seg = sl; seg < nseg; seg += SW) {
     const int64_t col0 = seg * GSEG + (int64_t)lane * 32;
+    // this lane's 32 activations as 16 fp16 pairs; columns >= n count as zero
+    uint32_t xr[16];
     if (col0 + 32 <= n && ((uintptr_t)x & 15) == 0) {
       const uint4* xp = reinterpret_cast<const uint4*>(x + col0);
 #pragma unroll
@@ -164,78 +216,25 @@ __global__ __launch_bounds__(64 * GNW, 4) __attribute__((amdgpu_num_sgpr(80))) v
         xr[u] = lo | (hi << 16);
       }
     }
-  };
-  // the code groups of this wavefront's rows, all fetched before any is used; a lane whose
-  // group lies outside the matrix fetches group 0 of row 0 instead and discards it
-  auto load_q = [&](int64_t seg, uint32_t (&q)[RPW][N]) {
-    const int64_t col0 = seg * GSEG + (int64_t)lane * 32;
+    // The code groups of this wavefront's rows, all fetched before any is used.  What differs between
+    // lanes is 32 bits of offset; a lane past the last column fetches the segment's first group, a row
+    // past the last one reads row 0, and both are discarded.
+    const uint32_t loff = (col0 < n) ? (uint32_t)lane * (4 * N) : 0u;
+    uint32_t q[RPW][N];
 #pragma unroll
     for (int k = 0; k < RPW; ++k) {
       const int64_t row = row0 + g + RG * k;
-      const bool ok = row < m && col0 < n;
-      const uint32_t* src = reinterpret_cast<const uint32_t*>(packed + (ok ? row : 0) * ldp) +
-                            (ok ? (seg * 64 + lane) * N : 0);
-      load_group<N>(src, q[k]);
+      const uint8_t* src = packed + (row < m ? row : 0) * ldp + seg * (64 * 4 * N);
+      load_group<N>(reinterpret_cast<const uint32_t*>(src + loff), q[k]);
+    }
+#pragma unroll
+    for (int k = 0; k < RPW; ++k) {
+      const bool ok = row0 + g + RG * k < m && col0 < n;
 #pragma unroll
       for (int w = 0; w < N; ++w) q[k][w] = ok ? q[k][w] : 0u;
     }
-  };
-  // At 4 bits and eight rows a wavefront the first segment is requested before the tables are built: each
-  // has one or few, and little else to hide their latency behind (28672 x 8192 40.1 -> 35.5 us, with
-  // outliers 58 -> 43).  With fewer rows the registers cost a workgroup per compute unit (11008 x 4096 10.4
-  // -> 11.9 us), at 3 bits and less the longer code costs more than it hides, and with sixteen rows there
-  // are no registers to wait in.
-  constexpr bool AHEAD = N == 4 && SW == 4;
-  uint32_t xr[16], q[RPW][N];
-  if (AHEAD && sl < nseg) {
-    load_x(sl, xr);
-    load_q(sl, q);
-  }
-  // outliers: every wavefront takes two of the 16 rows, 64 entries at a time; its own two where it has two
-  constexpr bool OWN = SW == 1;
-  int64_t ob[2], on[2];           // a row's first entry and their number, the same in every lane
-  int32_t oc[2];
-  float ov[2];
-  if constexpr (SPARSE) {
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      const int64_t row = row0 + (OWN ? g + RG * k : 2 * wave + k);
-      ob[k] = (row < m) ? row_ptr[row] : 0;
-      on[k] = (row < m) ? row_ptr[row + 1] - ob[k] : 0;
-    }
-  }
-
-  // the 16 rows' tables
-  for (int e = tid; e < GR * TW; e += 64 * GNW) {
-    const int r = e / TW, idx = e % TW;
-    uint32_t v = 0u;
-    if (row0 + r < m) {
-      const uint16_t* lr = lut + (row0 + r) * C;
-      v = PAIR ? ((uint32_t)lr[idx & (C - 1)] | ((uint32_t)lr[idx >> N] << 16)) : (uint32_t)lr[idx];
-    }
-    tab[r][idx] = v;
-  }
-  const uint32_t gbase = (uint32_t)g * (TW * 4u);   // this wavefront's rows are g, g + RG, ...
-  __syncthreads();
-  // the entries themselves are requested behind the tables: in front of them their two dependent reads
-  // hold up every wavefront of the workgroup
-  if constexpr (SPARSE) {
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      const bool ok = lane < on[k];
-      oc[k] = ok ? col_idx[ob[k] + lane] : 0;
-      ov[k] = ok ? values[ob[k] + lane] : 0.f;
-    }
-  }
-
-  float acc[RPW];
-#pragma unroll
-  for (int k = 0; k < RPW; ++k) acc[k] = 0.f;
-
-  for (int64_t seg = sl; seg < nseg; seg += SW) {
-    if (!AHEAD || seg != sl) {
-      load_x(seg, xr);
-      load_q(seg, q);
+    if constexpr (AHEAD) {
+      if (seg == sl) tables();
     }
     // Look-ups in batches (LB per row, two rows): the reads of the next batch are issued
     // before the previous batch is multiplied, and the scheduling barriers keep it that way
