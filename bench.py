@@ -155,8 +155,8 @@ def cpu_baseline(cfg, X_dev, W_dev, rows=256, tokens=16384):
 
 
 # HBM bytes per look-up-table product (FETCH_SIZE x 2.000 + WRITE_SIZE x 1.000, KiB per dispatch, from
-# rocprofv3); other shapes report null.
-TRAFFIC_DECODE_BYTES = {("c5", 4): (57757.9 * 2.000 + 32.0) * 1024}
+# profiles/decode_c5_kernel_stats.txt); other shapes report null.
+TRAFFIC_DECODE_BYTES = {("c5", 4): (57748.7 * 2.000 + 32.0) * 1024}
 
 
 def decode_main(args):

@@ -171,7 +171,8 @@ ganq_status ganq_init_codebooks(ganq_ctx* ctx, const void* W, ganq_dtype w_dtype
  * with r_iu = W_iu - T_i[Q_iu]; ties go to the lowest s.  W m x n fp32,
  * L n x n fp32 lower triangular with positive diagonal, T m x 2^nbits fp32,
  * Q m x n uint8 (one index per byte).  E (optional, may be NULL) receives the
- * residuals W - T[Q], m x n fp32 with leading dimension lde. */
+ * residuals W - T[Q], m x n fp32 with leading dimension lde.  A target that is
+ * NaN takes the lowest code. */
 ganq_status ganq_update_S(ganq_ctx* ctx, const float* W, int64_t m, int64_t n, int64_t ldw,
                           const float* L, int64_t ldl, const float* T, int nbits, uint8_t* Q,
                           int64_t ldq, float* E, int64_t lde);
@@ -302,13 +303,13 @@ typedef GANQ_ENUM {
   GANQ_K_CHOLESKY = 1, /* whole blocked factorisation */
   GANQ_K_INIT = 2,     /* T^0 (and fp16 -> fp32 conversion of W) */
   GANQ_K_GEMM_WH = 3,  /* G = W H, once per layer */
-  GANQ_K_UPDATE_S = 4, /* one S-update sweep (one launch) */
+  GANQ_K_UPDATE_S = 4, /* one S-update sweep (two launches per 1024 columns), with the first of a layer its operands */
   GANQ_K_T_PREP = 5,   /* integer digits of H for the T-update, once per layer */
   GANQ_K_T_PAD = 6,    /* padded copy of Q (and the list of changed columns), once per sweep */
   GANQ_K_T_ACCUM = 7,  /* one-hot GEMM of the T-update, once per sweep */
   GANQ_K_T_SOLVE = 8,  /* per-row assembly and solve, once per sweep */
   GANQ_K_LOSS = 9,     /* objective evaluation */
-  GANQ_K_OUTLIER = 10, /* outlier split (sort, offsets, compaction) */
+  GANQ_K_OUTLIER = 10, /* outlier split (selection, offsets, compaction) */
   GANQ_K_PACK = 11,    /* stored form: bit packing and fp16 tables */
   GANQ_K_LUT_GEMV = 12,/* look-up-table product for one activation vector */
   GANQ_K_T_DELTA = 13, /* update of S_i H S_i^T from the changed columns, in sweeps with few changes */

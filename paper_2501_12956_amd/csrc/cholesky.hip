@@ -419,8 +419,10 @@ __global__ __launch_bounds__(256) void chol_panel_kernel(const float* __restrict
 }  // namespace
 
 constexpr int kOuter = 4 * NB;
-// Trailing updates of more rows than this run on the fp16 units (split pieces, two launches).  Below,
-// the fp32 update takes at most 30 us, which the second launch and its pieces use up.
+// Trailing updates of more rows than this run on the fp16 units (split pieces, two launches).  The split
+// saves 3 % of a factorization of 5120, 7 % at 6656, 11 % at 8192 and 40 % at 28672; a line at 3072 or 2048
+// rows would save another 1 to 3 % from n = 4096 on and nothing below, not enough to leave fp32 products
+// for.
 constexpr int64_t kSplitRows = 4096;
 constexpr int kPanelLds = (4 * NB * BLD + NB * PLD) * (int)sizeof(float);
 
@@ -431,7 +433,7 @@ size_t cholesky_scratch_bytes(int64_t n) {
 
 hipError_t launch_cholesky(hipStream_t s, const float* H, int64_t n, int64_t ldh, int precond,
                            float lambda, float* L, int64_t ldl, int* info_dev) {
-  // info_dev points at scratch: [int info][pad to 256][float delta[n]][float thr[n]][float W[n x n]][pieces of a panel, large n][pieces of a panel]
+  // info_dev points at scratch: [int info][pad to 256][float delta[n]][float thr[n]][float W[n x n]][pieces of a panel, large n]
   float* delta = reinterpret_cast<float*>(reinterpret_cast<char*>(info_dev) + kAlign);
   float* thr = reinterpret_cast<float*>(reinterpret_cast<char*>(delta) + align_up((size_t)n * sizeof(float)));
   float* W = reinterpret_cast<float*>(reinterpret_cast<char*>(thr) + align_up((size_t)n * sizeof(float)));

@@ -26,8 +26,6 @@ struct ganq_ctx {
   std::vector<hipEvent_t> prof_free;
   double prof_ms[GANQ_K_COUNT] = {0};
   int64_t prof_launches[GANQ_K_COUNT] = {0};
-  // second stream (default priority) and two events: work of one call that does not depend on
-  // the factorisation runs beside it; always joined before the call returns
   // log of the last ganq_quantize_layer call (3 ints per sweep, see read_t_log) and its length
   int sweep_log[3 * 64] = {0};
   int sweep_log_len = 0;
@@ -45,6 +43,8 @@ struct ganq_ctx {
     float* G = nullptr;
     void* t_scratch = nullptr;
   } tprep;
+  // second stream (default priority) and two events: work of one call that does not depend on
+  // the factorisation runs beside it; always joined before the call returns
   hipStream_t side = nullptr;
   hipEvent_t fork_ev = nullptr, join_ev = nullptr;
 };

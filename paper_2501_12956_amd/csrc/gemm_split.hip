@@ -4,15 +4,17 @@
 // bits), and
 //     A B^T = Ahi Bhi^T + Ahi Blo^T + Alo Bhi^T        (+ Alo Blo^T, below 2^-22, dropped)
 // is accumulated in fp32 by v_mfma_f32_32x32x16_f16.  Used for G = W H (T-update, Eq. (7): H is
-// symmetric, so its rows serve as the rows of B) and for F = E H of the objective (Eq. (9)); both
-// have a relative tolerance of 1e-4 downstream.  The trailing updates of large Cholesky
-// factorizations have a kernel of their own here (pair_syrk256_kernel).
+// symmetric, so its rows serve as the rows of B), for F = E H of the objective (Eq. (9)) - both
+// have a relative tolerance of 1e-4 downstream - and for the columns far to the right in the
+// S-update.  The trailing updates of large Cholesky factorizations have a kernel of their own here
+// (pair_syrk256_kernel).
 //
 // Both pieces of 32 columns share one 128-byte line, [hi x 32 | lo x 32], so one LDS stage (32 k,
 // 256 + 256 lines) feeds all three piece products: 48 MFMAs per wavefront and stage, where reading
 // the pieces as three separate products moves 1.5 times the bytes per MFMA.  The product kernel is
 // the H = X X^T kernel's skeleton otherwise: 8 wavefronts of 128 x 64, tiles loaded straight into
-// LDS (buffer_load ... lds) with XOR-permuted 16-byte chunks, two stages, one barrier per step.
+// LDS (buffer_load ... lds) with XOR-permuted 16-byte chunks, two stages, one barrier per step;
+// small tiles are 4 wavefronts of 64 x 64, two workgroups per compute unit.
 // Bound by MFMA issue and power at large sizes: 8192 x 28672 x 28672 38.3 -> 32.0 ms (1.26 PFLOP/s
 // issued, what a large bf16 library product reaches on the same card), 4096^3 365 -> 320 us,
 // 2048^3 141 -> 66 us; making the pieces 26 + 10 -> 7 us per 2048 x 2048 operand (a row's exponent
@@ -239,7 +241,6 @@ __global__ __launch_bounds__(TILE * 2, 2) void pair_gemm_kernel(const _Float16* 
 // One wavefront per row of 256 columns: its exponent and its pieces (rows of 512 halves).
 __global__ __launch_bounds__(256) void pair_split256_kernel(const float* __restrict__ X, int64_t rows, int64_t ld,
                                                             _Float16* __restrict__ dst, int* __restrict__ ex) {
-  typedef _Float16 half4 __attribute__((ext_vector_type(4)));
   const int lane = threadIdx.x & 63;
   const int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (r >= rows) return;
@@ -400,10 +401,11 @@ hipError_t launch_pair_split(hipStream_t s, const float* X, int64_t rows, int64_
 // Mean error of its targets in units of 2^-24 of their size, with sums of everything to the right in
 // the fp32 matrix units / with large tiles (m = 8192) / now: 5000 columns 5.5 / 6.3 / 1.7, with the
 // dominant features on the left 2.7 / 8.1 / 2.0; 27648 columns 11.6 / 10.7 / 2.1.  It costs 2.4 of the
-// 22.4 ms of an 8192 x 28672 sweep.  Otherwise
-// 256 x 256 tiles where they give at least 3 of 4 compute units one; below that 128 x 128 tiles:
-// 2048 x 2048 products have 64 of the large tiles and take 141 us with
-// them, 66 us with 256 of the small ones (a tile's K walk is the same length either way).
+// 22.4 ms of an 8192 x 28672 sweep.  Otherwise 256 x 256 tiles where there are at least 192 of them, 128 x
+// 128 tiles below (G = W H with its pieces, large / small tiles: 64 large tiles, 2048 x 2048, 141 / 66 us;
+// 128, 2048 x 4096, 310 / 246; 144, 3072 x 3072, 226 / 246; 169, 252 / 282; 192, 4096 x 3072, 247 / 268; 256,
+// 4096 x 4096, 396 / 451).  Time alone would put the line near 140; between there and 192 the small
+// tiles' accuracy costs up to a tenth.
 hipError_t launch_pair_gemm(hipStream_t s, const _Float16* A, const _Float16* B, int64_t M, int64_t N, int64_t kp,
                             int step0, int step1, int splits, const int* ea, const int* eb, float* C, int64_t ldc,
                             int64_t cstride, bool small_tiles) {

@@ -18,7 +18,7 @@
 //              each decided residual updates the rest of the block and the whole next block
 //              (right-looking).  The other four meanwhile multiply, for the next block, the columns
 //              right of the current one (the same split products, residual pieces in LDS, pieces of L
-//              streamed from L2 up to 16 k steps ahead), stage the next 64 x 128 piece of L in LDS and
+//              streamed from L2 up to 12 k steps ahead), stage the next 64 x 128 piece of L in LDS and
 //              write out what the block before decided.  So a block costs its 64 dependent steps and one
 //              LDS-only barrier.  The product is not done on the fp32 matrix units because those hold
 //              up the vector unit of the deciding wavefront on the same SIMD: its steps got slower by
@@ -30,10 +30,13 @@
 // lanes with an exact one-hot lane-row sum (DPP).  A target exactly on a midpoint takes the lower
 // code; two equal codes resolve to the lower index.
 //
-// Bounds: the dependent steps (n x about 170 cycles, whatever m up to 16 rows per compute unit) and
-// the products (3 m n^2 flops on the fp16 units).
+// Infinite weights and NaN act as in an fp32 evaluation: the residual is that of the code written to
+// Q (the lowest for a target of -inf or NaN), and as pieces they travel in the low one alone.
+//
+// Bounds: the dependent steps (n x about 125 cycles and 1.2k cycles of hand-over per 64 of them,
+// whatever m up to 16 rows per compute unit) and the products (3 m n^2 flops on the fp16 units).
 // Measured per sweep, before (one workgroup walking all n columns, its sums over everything to the
-// right on the fp32 matrix units) and now: 4096 x 4096 0.94 -> 0.53 ms (87 us of sweep and 60 us of
+// right on the fp32 matrix units) and now: 4096 x 4096 0.94 -> 0.54 ms (88 us of sweep and 60 us of
 // products per super-block), 4096 x 11008 5.4 -> 2.5 ms, 8192 x 28672 71.4 -> 24.8 ms, 256 x 512
 // 62 -> 38 us.
 #include "ganq_internal.h"

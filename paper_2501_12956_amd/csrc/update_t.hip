@@ -52,7 +52,7 @@ namespace {
 
 constexpr int TM = 128;    // rows j of H per tile
 // Four wavefronts per workgroup, each 128 x 64 of the tile, and two workgroups per compute unit
-// (72 KB of LDS each): the two wavefronts that share a SIMD then belong to different workgroups
+// (60 to 80 KB of LDS each): the two wavefronts that share a SIMD then belong to different workgroups
 // and are not held to the same barrier, so one's staging work runs under the other's MFMAs.
 constexpr int TNW = 4;
 constexpr int TN = 64 * TNW;    // (row i, code b) pairs per workgroup
