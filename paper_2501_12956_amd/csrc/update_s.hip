@@ -256,7 +256,8 @@ __global__ __launch_bounds__(64 * NW) void update_S_kernel(const float* __restri
     tm = fmaxf(tm, dpp_f<0x141>(tm));
     tm = fmaxf(tm, dpp_f<0x140>(tm));
     tm += (row_ok && sb.wmax != nullptr) ? sb.wmax[row] : 0.f;
-    const int ea = (tm > 0.f && tm < __builtin_huge_valf()) ? 14 - ilogbf(tm) : 0;
+    // (the sum of two finite maxima may itself be out of range: it is below 2^129 then)
+    const int ea = (tm > 0.f) ? 14 - (tm < __builtin_huge_valf() ? ilogbf(tm) : 128) : 0;
     if (c == 0) {
       eal[r] = ea;
       if (sb.jhi == n && row_ok) sb.ea[row] = ea;     // for the products of the super-blocks to come

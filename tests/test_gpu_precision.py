@@ -178,3 +178,25 @@ def test_update_S_choices_with_remainders_in_every_direction(ctx, m, n, nbits):
     best = torch.stack([(tgt - Td[:, s:s + 1]).abs() for s in range(1 << nbits)]).amin(0)
     rel = (gap - best) / Td.abs().amax(1, keepdim=True)
     assert rel.max().item() < 1e-6
+
+
+@pytest.mark.parametrize("n", [300, 2100])
+def test_update_S_follows_the_scale_of_a_row(ctx, n):
+    """Scaling a row of W and of T by a power of two scales its targets exactly, so its choices stay, up to
+    rows whose largest weight and code add up to more than fp32 holds."""
+    m, nbits = 6, 4
+    g = torch.Generator(device="cuda").manual_seed(n)
+    W1 = torch.randn(1, n, generator=g, device="cuda")
+    W1 = W1 / W1.abs().max() * 1.9
+    L = torch.randn(n, n, generator=g, device="cuda").tril_(-1) * (0.3 / n ** 0.5)
+    L.diagonal().fill_(1.0)
+    T1 = ctx.init_codebooks(W1, nbits)
+    T1 = T1.clamp(-0.95, 0.95)              # the midpoint of two codes forms their sum, which stays in range
+    T1[0, 0], T1[0, 15] = -1.0, 1.0
+    k = torch.tensor([0.0, -90.0, -20.0, 60.0, 126.0, 127.0], device="cuda", dtype=torch.float64)
+    s = torch.exp2(k)[:, None]
+    W, T = (W1.double() * s).float().contiguous(), (T1.double() * s).float().contiguous()
+    Q = ctx.update_S(W, L, T, nbits)
+    assert bool(torch.isfinite(W).all()) and bool(torch.isfinite(T).all())
+    for i in range(1, m):
+        assert torch.equal(Q[i], Q[0]), i
