@@ -12,21 +12,29 @@
 // registers are held across the MFMA block and no LDS store instructions are issued.  Such
 // a load writes 64 x 16 bytes to consecutive LDS addresses, so the LDS tile cannot be
 // padded; instead the 16-byte chunks of a row are stored in an XOR-permuted order
-// (chunk c of row r at position c ^ (r & 7)), which the lanes apply on the global side
-// when they choose what to fetch and on the LDS side when they read MFMA fragments.
+// (chunk c of row r at position c ^ ((r >> 1) & 7)), which the lanes apply on the global side
+// when they choose what to fetch and on the LDS side when they read MFMA fragments.  A 16-byte LDS
+// read serves 16 lanes at a time, so 16 consecutive rows must fall into different banks: a
+// permutation that repeated after 8 rows doubled the time of every fragment read (by the counters).
 #include "ganq_internal.h"
 
 namespace ganq {
 namespace {
 
 constexpr int HT = kHessTile;   // 256 x 256 output tile per workgroup
-constexpr int HK = 64;          // tokens per LDS stage: one 128-byte line per row
-constexpr int HS = 2;           // LDS stages
-constexpr int HROWB = HK * 2;   // bytes per LDS row
-constexpr int HTILEB = HT * HROWB;
-constexpr int HSTAGEB = 2 * HTILEB;          // A rows + B rows
+// tokens per LDS stage, stages, bytes per LDS row, direct loads per wavefront, operand and stage: 128-byte
+// lines of feature-major activations in two stages, runs of 512 bytes of token-major ones in five
+constexpr int hk(bool tok) { return tok ? 32 : 64; }
+constexpr int hs(bool tok) { return tok ? 5 : 2; }
+constexpr int HCHUNK = 64;      // a split's tokens are whole multiples of this many
+constexpr int HROWB = 128;      // feature-major stage: bytes per feature row (64 tokens)
+constexpr int htileb(bool tok) { return HT * hk(tok) * 2; }
+constexpr int hstageb(bool tok) { return 2 * htileb(tok); }      // A rows + B rows
 constexpr int HNW = 8;          // wavefronts: 2 x 4, each 128 x 64 of the tile
-constexpr int HDPW = (HT / 8) / HNW;         // direct loads per wavefront, operand and stage
+
+// All but the newest N of this wavefront's direct loads have arrived.
+template <int N>
+__device__ inline void wait_loads_but() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 
 constexpr int TROWB = HT * 2;   // token-major stage: bytes per token row (256 features)
 
@@ -41,6 +49,17 @@ __device__ inline half8 tr_fragment(const unsigned char* p) {
   const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4*)(uintptr_t)(p + 4 * TROWB));
   return __builtin_shufflevector(__builtin_bit_cast(half4v, lo), __builtin_bit_cast(half4v, hi), 0, 1, 2, 3, 4,
                                  5, 6, 7);
+}
+
+// Asks the scheduler for the fragment reads of the next half step spread over the eight MFMAs of this one.
+template <bool TOK>
+__device__ inline void interleave() {
+#pragma unroll
+  for (int u = 0; u < 6; ++u) {
+    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+    __builtin_amdgcn_sched_group_barrier(0x100, TOK ? 2 : 1, 0);
+  }
+  __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
 }
 
 // Tiles (r, c), c <= r < nt, of the lower triangle in Z-order (bits of c and r interleaved, c
@@ -87,9 +106,18 @@ __device__ inline void zorder_tile(int t, int nt, int& bm, int& bn) {
 }
 
 // 8 wavefronts (2 per SIMD) in a 2 x 4 grid, each owning 128 x 64 of the tile as 4 x 2 MFMA
-// tiles of 32 x 32 (128 accumulator registers).  Two LDS stages of 64 tokens, one barrier
-// per stage: after the barrier the loads of the next stage are issued into the buffer that
-// every wavefront has just finished reading, then the current stage is multiplied.
+// tiles of 32 x 32 (128 accumulator registers).  The fragments of a step of 16 tokens are read under the
+// MFMAs of the step before.  Feature-major: two LDS stages of 64 tokens, so that a row's loads are whole
+// 128-byte lines (five stages of 32 tokens, half a line each, have as few
+// cycles and took 2 % longer at 11008 x 262144: twice the requests).  Token-major, whose loads are runs of
+// 512 bytes anyway: five stages of 32 tokens fill the 160 KB, three of them in flight, a wavefront waits
+// for all but its newest loads by count, and the reads ahead go across the barrier.
+// With reads that the compiler placed in front of their MFMAs and banks met twice the loop took 1531
+// (token-major 1611) cycles per 32 tokens, now 1354 (1394), of which 1024 are MFMA issue.  What that
+// gives in time is limited by power: with more of the matrix unit busy the clock goes down (1.43 -> 1.30
+// and 1.63 -> 1.48 GHz; 4096 x 65536 1136 -> 1089 us and 1150 -> 1075 us; one pass over 2048 tokens
+// 68 -> 65 and 70.5 -> 66.5 us).  Without any loads it would be 860 us at 1.6 GHz.  Four wavefronts of
+// 128 x 128 took 1205 (1105) us.
 //
 // TOK: X is the token-major array Xt (p x n, tokens x features, leading dimension ldx) and
 // H = Xt^T Xt.  A stage then holds 64 token rows of 256 features per operand (512-byte rows), and
@@ -99,8 +127,8 @@ __device__ inline void zorder_tile(int t, int nt, int& bm, int& bn) {
 // addresses token e of a run of four and features 4a .. 4a + 3 of a run of 16, so lane f of the
 // group ends up with tokens 0..3 of feature f.  Both operands take the same path, so the order in
 // which tokens land in a fragment is the same on both sides of every product.  16-byte chunk c of
-// token row t is stored at position c ^ 2 (t & 3): the four token rows a group reads then fall
-// into four different 32-byte bank groups.
+// token row t is stored at position c ^ 4 (t & 3): the two groups of 16 lanes that are served
+// together then fall into eight different 32-byte bank groups.
 template <bool TOK>
 __global__ __launch_bounds__(64 * HNW) void hessian_f16_kernel(const _Float16* __restrict__ X, int64_t n,
                                                               int64_t p, int64_t ldx, int64_t chunk,
@@ -121,6 +149,9 @@ __global__ __launch_bounds__(64 * HNW) void hessian_f16_kernel(const _Float16* _
   const int64_t kbeg = (int64_t)split * chunk;
   const int64_t kend = (kbeg + chunk < p) ? kbeg + chunk : p;
 
+  constexpr int HK = hk(TOK), HS = hs(TOK), HTILEB = htileb(TOK), HSTAGEB = hstageb(TOK);
+  constexpr int HDPW = HTILEB / 1024 / HNW;    // direct loads per wavefront, operand and stage
+  constexpr int HLPS = 2 * HDPW;               // of both operands
   extern __shared__ __attribute__((aligned(16))) unsigned char hsm[];
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)hsm;
 
@@ -140,9 +171,9 @@ __global__ __launch_bounds__(64 * HNW) void hessian_f16_kernel(const _Float16* _
     rsA = make_rsrc(X + m0 * ldx, ((rowsA - 1) * ldx + p) * 2);
     rsB = make_rsrc(X + n0 * ldx, ((rowsB - 1) * ldx + p) * 2);
     // One direct load covers 8 rows x 128 bytes: lane -> row (lane / 8) and LDS chunk position
-    // (lane % 8), which holds chunk position ^ (row & 7) of the row.
+    // (lane % 8), which holds chunk position ^ ((row >> 1) & 7) of the row.
     const int dr = lane >> 3;
-    const int dc = (lane & 7) ^ dr;
+    const int dc = (lane & 7) ^ (((wave & 1) << 2) | (dr >> 1));      // HNW is even
 #pragma unroll
     for (int j = 0; j < HDPW; ++j) {
       voff[j] = (uint32_t)(((int64_t)((wave + HNW * j) * 8 + dr) * ldx + dc * 8) * 2);
@@ -164,11 +195,11 @@ __global__ __launch_bounds__(64 * HNW) void hessian_f16_kernel(const _Float16* _
     rsA = make_rsrc(X + kbeg * ldx + m0, span(kbeg * ldx + m0));
     rsB = make_rsrc(X + kbeg * ldx + n0, span(kbeg * ldx + n0));
     // One direct load covers 2 token rows x 512 bytes: lane -> token row (lane / 32) and LDS
-    // chunk position (lane % 32), which holds chunk position ^ 2 (token & 3) of the row.
+    // chunk position (lane % 32), which holds chunk position ^ 4 (token & 3) of the row.
 #pragma unroll
     for (int j = 0; j < HDPW; ++j) {
       const int tl = 2 * (wave + HNW * j) + (lane >> 5);
-      const int cg = (lane & 31) ^ (2 * (tl & 3));
+      const int cg = (lane & 31) ^ (4 * (tl & 3));
       const uint32_t vo = (uint32_t)(((int64_t)tl * ldx + cg * 8) * 2);
       voff[j] = (m0 + cg * 8 < n) ? vo : 0x80000000u;
       voffB[j] = (n0 + cg * 8 < n) ? vo : 0x80000000u;
@@ -176,11 +207,14 @@ __global__ __launch_bounds__(64 * HNW) void hessian_f16_kernel(const _Float16* _
     }
   }
 
-  auto issue = [&](int64_t k0, int st) {
+  const int nk = (int)((kend - kbeg + HK - 1) / HK);
+  // Requests run past the last step: their lanes read nothing (offsets beyond any descriptor).
+  auto issue = [&](int k, int st) {
     const uint32_t sbase = lds0 + st * HSTAGEB;
+    const int64_t k0 = kbeg + (int64_t)k * HK, ks = kbeg + (int64_t)(k < nk ? k : nk - 1) * HK;
     if constexpr (!TOK) {
       const bool ok = k0 + klane < kend;     // p % 8 == 0: a chunk is wholly inside or outside
-      const uint32_t soff = (uint32_t)(k0 * 2);
+      const uint32_t soff = (uint32_t)(ks * 2);
 #pragma unroll
       for (int j = 0; j < HDPW; ++j) {
         const uint32_t vo = ok ? voff[j] : 0x80000000u;   // beyond any descriptor: reads zero
@@ -188,7 +222,7 @@ __global__ __launch_bounds__(64 * HNW) void hessian_f16_kernel(const _Float16* _
         load16_to_lds(rsB, sbase + HTILEB + (wave + HNW * j) * 1024, vo, soff);
       }
     } else {
-      const uint32_t soff = (uint32_t)((k0 - kbeg) * ldx * 2);      // below 2^31: checked by the host
+      const uint32_t soff = (uint32_t)((ks - kbeg) * ldx * 2);      // below 2^31: checked by the host
 #pragma unroll
       for (int j = 0; j < HDPW; ++j) {
         const bool ok = k0 + tlane[j] < kend;
@@ -206,7 +240,7 @@ __global__ __launch_bounds__(64 * HNW) void hessian_f16_kernel(const _Float16* _
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
-  const int rswz = l32 & 7;
+  const int rswz = (l32 >> 1) & 7;
   // TOK: byte offset, inside a stage, of this lane's 8-byte piece for each of the wavefront's
   // fragments: token row 8 (lane / 32) + e, chunk (feature / 8) ^ 2 e, half chunk a & 1
   uint32_t toffA[4], toffB[2];
@@ -215,47 +249,93 @@ __global__ __launch_bounds__(64 * HNW) void hessian_f16_kernel(const _Float16* _
     const uint32_t rowb = (uint32_t)((8 * kh + e) * TROWB + 8 * (a & 1));
 #pragma unroll
     for (int i = 0; i < 4; ++i)
-      toffA[i] = rowb + (uint32_t)(((wr * 16 + i * 4 + 2 * g1 + (a >> 1)) ^ (2 * e)) * 16);
+      toffA[i] = rowb + (uint32_t)(((wr * 16 + i * 4 + 2 * g1 + (a >> 1)) ^ (4 * e)) * 16);
 #pragma unroll
     for (int j = 0; j < 2; ++j)
-      toffB[j] = rowb + (uint32_t)(((wc * 8 + j * 4 + 2 * g1 + (a >> 1)) ^ (2 * e)) * 16);
+      toffB[j] = rowb + (uint32_t)(((wc * 8 + j * 4 + 2 * g1 + (a >> 1)) ^ (4 * e)) * 16);
   }
-  const int nk = (int)((kend - kbeg + HK - 1) / HK);
-  if (nk > 0) issue(kbeg, 0);
-  int st = 0;
-#pragma unroll 1
-  for (int k = 0; k < nk; ++k) {
-    wait_all_loads();
-    __syncthreads();
-    if (k + 1 < nk) issue(kbeg + (int64_t)(k + 1) * HK, st ^ 1);
+  struct Frags {
+    half8 a[4], b[2];
+  };
+  auto load_frags = [&](Frags& f, int st, int ks) {
     const unsigned char* As = hsm + st * HSTAGEB;
     const unsigned char* Bs = As + HTILEB;
-#pragma unroll
-    for (int ks = 0; ks < HK / 16; ++ks) {
-      half8 af[4], bfr[2];
-      if constexpr (!TOK) {
-        const int cpos = ((2 * ks + kh) ^ rswz) * 16;
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-          af[i] = *reinterpret_cast<const half8*>(As + (wr * 128 + i * 32 + l32) * HROWB + cpos);
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-          bfr[j] = *reinterpret_cast<const half8*>(Bs + (wc * 64 + j * 32 + l32) * HROWB + cpos);
-      } else {
-        const unsigned char* Ak = As + ks * (16 * TROWB);
-        const unsigned char* Bk = Bs + ks * (16 * TROWB);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) af[i] = tr_fragment(Ak + toffA[i]);
-#pragma unroll
-        for (int j = 0; j < 2; ++j) bfr[j] = tr_fragment(Bk + toffB[j]);
-      }
+    if constexpr (!TOK) {
+      const int cpos = ((2 * ks + kh) ^ rswz) * 16;
 #pragma unroll
       for (int i = 0; i < 4; ++i)
+        f.a[i] = *reinterpret_cast<const half8*>(As + (wr * 128 + i * 32 + l32) * HROWB + cpos);
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(af[i], bfr[j], acc[i][j], 0, 0, 0);
+      for (int j = 0; j < 2; ++j)
+        f.b[j] = *reinterpret_cast<const half8*>(Bs + (wc * 64 + j * 32 + l32) * HROWB + cpos);
+    } else {
+      const unsigned char* Ak = As + ks * (16 * TROWB);
+      const unsigned char* Bk = Bs + ks * (16 * TROWB);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) f.a[i] = tr_fragment(Ak + toffA[i]);
+#pragma unroll
+      for (int j = 0; j < 2; ++j) f.b[j] = tr_fragment(Bk + toffB[j]);
     }
-    st ^= 1;
+  };
+  auto mma = [&](const Frags& f) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(f.a[i], f.b[j], acc[i][j], 0, 0, 0);
+  };
+  Frags f0, f1;
+  if constexpr (TOK) {
+    if (nk > 0) {
+#pragma unroll
+      for (int u = 0; u < HS - 1; ++u) issue(u, u);
+      wait_loads_but<(HS - 2) * HLPS>();
+      __syncthreads();
+      load_frags(f0, 0, 0);
+    }
+    int st = 0, sn = HS - 1;
+#pragma unroll 1
+    for (int k = 0; k < nk; ++k) {
+      const int st1 = (st == HS - 1) ? 0 : st + 1;
+      wait_loads_but<(HS - 3) * HLPS>();
+      __syncthreads();
+      issue(k + HS - 1, sn);
+      sn = (sn == HS - 1) ? 0 : sn + 1;
+      __builtin_amdgcn_sched_barrier(0);
+      load_frags(f1, st, 1);
+      mma(f0);
+      interleave<TOK>();
+      __builtin_amdgcn_sched_barrier(0);
+      load_frags(f0, st1, 0);
+      mma(f1);
+      interleave<TOK>();
+      __builtin_amdgcn_sched_barrier(0);
+      st = st1;
+    }
+    wait_all_loads();
+  } else {
+    if (nk > 0) issue(0, 0);
+    int st = 0;
+#pragma unroll 1
+    for (int k = 0; k < nk; ++k) {
+      wait_all_loads();
+      __syncthreads();
+      if (k + 1 < nk) issue(k + 1, st ^ 1);
+      load_frags(f0, st, 0);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int ks = 0; ks < HK / 16; ks += 2) {
+        load_frags(f1, st, ks + 1);
+        mma(f0);
+        interleave<TOK>();
+        __builtin_amdgcn_sched_barrier(0);
+        if (ks + 2 < HK / 16) load_frags(f0, st, ks + 2);
+        mma(f1);
+        if (ks + 2 < HK / 16) interleave<TOK>();
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      st ^= 1;
+    }
   }
 
   float* out = partials + (int64_t)split * n * n;
@@ -370,17 +450,17 @@ hipError_t launch_hessian_f16(hipStream_t s, const _Float16* X, int64_t n, int64
                               float* H, int64_t ldh, int accumulate, float* partials) {
   if (ldx >= ((int64_t)1 << 22) || (p % 8) != 0 || (ldx % 8) != 0) return hipErrorInvalidValue;
   const int split = hessian_split(n, p);
-  int64_t chunk = ceil_div(ceil_div(p, split), HK) * HK;
+  int64_t chunk = ceil_div(ceil_div(p, split), HCHUNK) * HCHUNK;
   const int64_t nt = ceil_div(n, HT);
   const int ntiles = (int)(nt * (nt + 1) / 2);
   const int ngroups = (int)ceil_div(ntiles, 32), gsz = (int)ceil_div(ntiles, ngroups);
   dim3 grid((unsigned)(8 * ceil_div((int64_t)ngroups * split, 8) * 32));
   static std::atomic<uint64_t> lds_set{0};
   {
-    const hipError_t ea = ensure_dynamic_lds((const void*)hessian_f16_kernel<false>, HS * HSTAGEB, lds_set);
+    const hipError_t ea = ensure_dynamic_lds((const void*)hessian_f16_kernel<false>, hs(false) * hstageb(false), lds_set);
     if (ea != hipSuccess) return ea;
   }
-  hipLaunchKernelGGL(hessian_f16_kernel<false>, grid, dim3(64 * HNW), HS * HSTAGEB, s, X, n, p, ldx, chunk,
+  hipLaunchKernelGGL(hessian_f16_kernel<false>, grid, dim3(64 * HNW), hs(false) * hstageb(false), s, X, n, p, ldx, chunk,
                      (int)nt, ntiles, ngroups, gsz, split, partials);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -396,8 +476,8 @@ bool hessian_tokens_direct_ok(const void* Xt, int64_t n, int64_t p, int64_t ldxt
   if (p <= 0 || (((uintptr_t)Xt) & 15) != 0 || (ldxt % 8) != 0 || (n % 8) != 0) return false;
   if (ldxt >= ((int64_t)1 << 23)) return false;       // 64 token rows within 31-bit lane offsets
   const int split = hessian_split(n, p);
-  const int64_t chunk = ceil_div(ceil_div(p, split), HK) * HK;
-  return (chunk + HK) * ldxt * 2 <= ((int64_t)1 << 31);
+  const int64_t chunk = ceil_div(ceil_div(p, split), HCHUNK) * HCHUNK;
+  return (chunk + HCHUNK) * ldxt * 2 <= ((int64_t)1 << 31);
 }
 
 // H (+)= Xt^T Xt straight from the token-major array; requires hessian_tokens_direct_ok.
@@ -405,17 +485,17 @@ hipError_t launch_hessian_f16_tokens(hipStream_t s, const _Float16* Xt, int64_t 
                                      float* H, int64_t ldh, int accumulate, float* partials) {
   if (!hessian_tokens_direct_ok(Xt, n, p, ldxt)) return hipErrorInvalidValue;
   const int split = hessian_split(n, p);
-  const int64_t chunk = ceil_div(ceil_div(p, split), HK) * HK;
+  const int64_t chunk = ceil_div(ceil_div(p, split), HCHUNK) * HCHUNK;
   const int64_t nt = ceil_div(n, HT);
   const int ntiles = (int)(nt * (nt + 1) / 2);
   const int ngroups = (int)ceil_div(ntiles, 32), gsz = (int)ceil_div(ntiles, ngroups);
   dim3 grid((unsigned)(8 * ceil_div((int64_t)ngroups * split, 8) * 32));
   static std::atomic<uint64_t> lds_set{0};
   {
-    const hipError_t ea = ensure_dynamic_lds((const void*)hessian_f16_kernel<true>, HS * HSTAGEB, lds_set);
+    const hipError_t ea = ensure_dynamic_lds((const void*)hessian_f16_kernel<true>, hs(true) * hstageb(true), lds_set);
     if (ea != hipSuccess) return ea;
   }
-  hipLaunchKernelGGL(hessian_f16_kernel<true>, grid, dim3(64 * HNW), HS * HSTAGEB, s, Xt, n, p, ldxt, chunk,
+  hipLaunchKernelGGL(hessian_f16_kernel<true>, grid, dim3(64 * HNW), hs(true) * hstageb(true), s, Xt, n, p, ldxt, chunk,
                      (int)nt, ntiles, ngroups, gsz, split, partials);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
