@@ -29,8 +29,8 @@
 // Only k < j is visited (H is symmetric):
 //   M_i[a, b] = sum_j [Q_ij == a] Z[j, (i,b)],   A_i = M_i + M_i^T + Diag(D_i),
 //   D_i[a] = sum_{j: Q_ij == a} H_jj.
-// The fold over j runs on the matrix cores as well, straight from the accumulator
-// registers and with the row factor 2^-s_j as the left operand (see t_accum_kernel); partial
+// The fold over j runs on the matrix cores as well, in int8 digits of the sums with one-hot entries that
+// carry the row factors (see t_accum_kernel); partial
 // M_i per group of row tiles of H go to scratch and are summed in float64 by the solve
 // kernel, which also forms D_i and b_i, drops unused codes (pseudo-inverse reading: their
 // entry is 0, or kept) and solves the reduced system by Cholesky in float64.
@@ -45,6 +45,8 @@
 // update pays off below about 3.5 % changed indices (t_delta_kernel; the choice is made on the
 // device, per sweep, from the counts of the kernel that lists the changes).  The state A_i is kept
 // in float64 and every change is an exact integer sum scaled by a power of two.
+#include <type_traits>
+
 #include "ganq_internal.h"
 
 namespace ganq {
@@ -56,7 +58,6 @@ constexpr int TM = 128;    // rows j of H per tile
 // and are not held to the same barrier, so one's staging work runs under the other's MFMAs.
 constexpr int TNW = 4;
 constexpr int TN = 64 * TNW;    // (row i, code b) pairs per workgroup
-constexpr int TK = 64;     // k per stage
 constexpr int TP = 4;      // most base-256 digits per entry
 constexpr int EMAX = 6;    // largest column exponent (the one-hot entry 2^e is an int8)
 constexpr float V2MAX = 32512.f;     // largest |v| with two digits:  127 * 256 + 127 - 127
@@ -125,6 +126,16 @@ constexpr int TF_THREE = 1, TF_SUM2 = 2, TF_SUM3 = 4, TF_FOUR = 8;
 __device__ __host__ inline int tile_digits(int flags) {
   return (flags & TF_FOUR) ? 4 : (flags & TF_THREE) ? 3 : 2;
 }
+// exponent s_j of a row by the number of its tile's digits
+__device__ inline int tile_exponent(int P, int s2, int s3) { return P == 2 ? s2 : P == 3 ? s3 : s3 + 8; }
+// 2^(f - 7 p) for the rows of round p of the fold, 0 for others
+__device__ inline uint8_t fold_factor(int f, int p) {
+  f -= 7 * p;
+  return (uint8_t)((f >= 0 && f < 7) ? 1 << f : 0);
+}
+// largest exponent of the tile's rows; rounds of its fold (both set by t_symscale_kernel)
+__device__ inline int tile_smax(int flags) { return ((flags >> 8) & 0xfff) - 256; }
+__device__ inline int tile_rounds(int flags) { return flags >> 20; }
 __device__ __host__ inline bool tile_shared_acc(int flags) {
   if (flags & TF_FOUR) return false;
   return (flags & ((flags & TF_THREE) ? TF_SUM3 : TF_SUM2)) == 0;
@@ -209,7 +220,7 @@ __global__ __launch_bounds__(256) void t_split_kernel(const float* __restrict__ 
   const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;      // column
   if (k >= npad) return;
   const int P = tile_digits(Ptile[j / TM]);
-  const int sj = (j < n) ? ((P == 2) ? S2[j] : (P == 3) ? S3[j] : S3[j] + 8) : 0;
+  const int sj = (j < n) ? tile_exponent(P, S2[j], S3[j]) : 0;
   if (k == 0) Wj[j] = ldexpf(1.f, -sj);
   int iv = 0;
   if (j < n && k < n && k != j) {
@@ -242,10 +253,11 @@ __global__ __launch_bounds__(256) void t_split_kernel(const float* __restrict__ 
 // choice is made here when it costs no precision - every tile at two digits, s the largest value
 // that keeps every row inside 16 bits, and every row still as fine as the two-digit rule asks -
 // and then the update is allowed; otherwise the per-row exponents stay and every sweep sums.
-__global__ __launch_bounds__(1024) void t_symscale_kernel(const int* __restrict__ Ptile, int mtiles, int64_t n,
+__global__ __launch_bounds__(1024) void t_symscale_kernel(int* __restrict__ Ptile, int mtiles, int64_t n,
                                                           int allow, const uint8_t* __restrict__ Cs,
                                                           int8_t* __restrict__ S2,
-                                                          const int16_t* __restrict__ Sneed,
+                                                          const int8_t* __restrict__ S3, int64_t npad,
+                                                          int16_t* __restrict__ Sneed,
                                                           int* __restrict__ Tstat) {
   __shared__ int red[1024];
   const int tid = threadIdx.x;
@@ -282,11 +294,41 @@ __global__ __launch_bounds__(1024) void t_symscale_kernel(const int* __restrict_
     Tstat[2] = 0;       // no state yet
     Tstat[3] = ok;
     Tstat[4] = 0;
+    Tstat[5] = 1;
+  }
+  // Row factors of the fold of full sweeps: 2^-s_j = 2^-smax 2^f_j with smax the tile's largest s_j; what
+  // goes into the int8 operand is 2^f_j, up to 2^6 a round.  Bytes of the first round over Sneed, which
+  // nobody reads any more; smax and the number of rounds beside the tile's flags.
+  __syncthreads();
+  uint8_t* F = reinterpret_cast<uint8_t*>(Sneed);
+  const int lane = tid & 63;
+  for (int t = tid >> 6; t < mtiles; t += 16) {
+    const int P = tile_digits(Ptile[t]);
+    const int64_t j0 = (int64_t)t * TM + lane, j1 = j0 + 64;
+    const int s0 = j0 < n ? tile_exponent(P, S2[j0], S3[j0]) : -1000, s1 = j1 < n ? tile_exponent(P, S2[j1], S3[j1]) : -1000;
+    int hi = s0 > s1 ? s0 : s1, lo = hi;
+    if (s0 > -1000) lo = min(lo, s0);
+    if (s1 > -1000) lo = min(lo, s1);
+    if (hi == -1000) lo = 1000;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      hi = max(hi, __shfl_xor(hi, o, 64));
+      lo = min(lo, __shfl_xor(lo, o, 64));
+    }
+    F[j0] = fold_factor(hi - s0, 0);
+    F[j1] = fold_factor(hi - s1, 0);
+    if (lane == 0) {
+      const int flags = Ptile[t] | (hi + 256) << 8 | ((hi - lo) / 7 + 1) << 20;
+      Ptile[t] = flags;
+      reinterpret_cast<int*>(F + npad)[t] = hi;       // 4 / TM of a byte per row: F and this fit Sneed (2 npad bytes)
+      if (P != 2 || !tile_shared_acc(flags) || tile_rounds(flags) != 1) Tstat[5] = 0;
+    }
   }
 }
 
 // Tstat: [0] largest number of changed indices in a row, [1] their total, [2] A-state valid,
-// [3] updates allowed for this layer, [4] number of 64-column chunks of changed columns.  The same
+// [3] updates allowed for this layer, [4] number of 64-column chunks of changed columns, [5] every tile
+// has two digits in one integer and rows that fold in one round.  The same
 // test in every kernel of a sweep: update when at most 1 / kDeltaInv of the indices changed.
 constexpr int kDeltaInv = 24;
 constexpr int kDeltaChunk = 32;
@@ -605,58 +647,93 @@ __global__ __launch_bounds__(256, 3) void t_delta_kernel(const int8_t* __restric
 
 // ---- the GEMM with fold epilogue ----
 // LDS: stages of { A tile: TM rows x 64 bytes (one digit of 64 k); the codes of the slab's rows, 64
-// bytes each; the one-hot values of these columns }.  Everything arrives by direct-to-LDS buffer
-// loads, every wavefront issuing the same number per stage, so a wavefront waits for all but the
-// newest stages by count; such a load writes 64 x 16 consecutive bytes, so rows cannot be padded and
-// the 16-byte chunks of a row of A are stored in XOR-permuted order (chunk c of row r at
-// c ^ ((r >> 1) & 3)).
+// bytes each; the one-hot values of these columns; the fold's factors of the rows of the same numbers }.
+// Everything arrives by direct-to-LDS buffer loads, every wavefront issuing the same number per stage, so
+// a wavefront waits for all but the newest stages by count; such a load writes 64 x 16 consecutive bytes, so
+// rows cannot be padded and the 16-byte chunks of a row of A are stored in XOR-permuted order (chunk c of
+// row r at c ^ ((r >> 2) & 3): the 16 rows that one LDS read serves fall into different banks).
 // The one-hot operand never exists in memory: a lane's 16 bytes of it belong to one row i, one code
 // b and 16 consecutive k, and come out of the 16 codes Q_ik with three operations per four of them.
-// It used to be a tile in LDS whose entries each thread moved with byte stores.  Bound by matrix and
-// vector issue together (an MFMA of 32 cycles and its three vector operations take 52): per summing sweep
-// 4096 x 4096 1.05 -> 0.96 ms, 8192 x 28672 79.0 -> 71.7 ms, 2048 x 2048 153 -> 143 us, 1537 x 2203 at
-// 3 bits 175 -> 138 us.  With the codes loaded into registers a step ahead and no order asked of the
-// scheduler the same operand took as long as the LDS tile (80.9 ms at 8192 x 28672).
+//
+// Bound by power at large n (the clock is 1.6 to 2.1 GHz), by what stands between the k-loops at small n.
+// Vector operations, LDS reads and requests cost nothing beside an int8 MFMA as long as no more than its 32
+// cycles hide stand behind it, none waits for the one before it, and direct loads are apart; so the order
+// of the k-step is given.  (An fp32 MFMA does hold up the vector unit; the fold used 128 of them.)  With reads
+// and requests at the top of a step and the fold in fp32: 2048 x 2048 148 -> 136 us, 1537 x 2203 at 3 bits 138 ->
+// 120, 256 x 512 (three digits) 52 -> 41, 4096 x 4096 953 -> 913, 8192 x 28672 72.7 -> 70.8 ms.
+constexpr int TK = 64;     // k per stage
 constexpr int T_ROWB = TK;
 constexpr int T_ATILEB = TM * T_ROWB;
-// 1 KB loads per wavefront and stage for the codes (TN / C rows of 64 bytes) and the one-hot values
-constexpr int t_code_loads(int nbits) { return ((TN >> nbits) / 16 + 1 + TNW - 1) / TNW; }
+// 1 KB loads per wavefront and stage for the codes (TN / C rows of 64 bytes), one-hot values and factors
+constexpr int t_code_loads(int nbits) { return ((TN >> nbits) / 16 + 2 + TNW - 1) / TNW; }
 constexpr int t_stage_bytes(int nbits) { return T_ATILEB + t_code_loads(nbits) * TNW * 1024; }
-// stages: as many as leave two workgroups per compute unit room
-constexpr int t_stages(int nbits) { return nbits >= 3 ? 5 : 4; }
+// stages: as many as leave two workgroups per compute unit room (and a kilobyte for requests past the end)
+constexpr int t_stages(int nbits) { return nbits >= 3 ? 5 : nbits == 2 ? 4 : 3; }
 
-// Bytes of cs where the code in q equals the one in b (both repeated or packed per byte, below 16),
-// zero elsewhere: (q ^ b) + 12 is 12 on a match and 13 to 27 otherwise, and as a selector of v_perm
-// 12 yields the byte 0x00, anything above 0xff.
-__device__ inline uint32_t one_hot4(uint32_t q, uint32_t b, uint32_t cs) {
-  const uint32_t off = __builtin_amdgcn_perm(0u, 0u, (q ^ b) + 0x0c0c0c0cu);
-  return cs & ~off;
+// Bytes of cs where the code in q equals this lane's, zero elsewhere.  Four bits: (q ^ b) + 12 is 12 on a
+// match and 13 to 27 otherwise, and as a selector of v_perm 12 yields the byte 0x00, anything above
+// 0xff.  Fewer bits: the code itself selects a byte of an eight-entry table that is 0xff at b.
+template <int NBITS>
+struct OneHotMaker {
+  uint32_t b, tlo, thi;
+  __device__ explicit OneHotMaker(int code)
+      : b((uint32_t)code * 0x01010101u),
+        tlo(code < 4 ? 0xffu << (8 * code) : 0u),
+        thi(code >= 4 ? 0xffu << (8 * (code & 3)) : 0u) {}
+  // the operations one by one (the first only at four bits), for callers that keep dependent ones apart
+  __device__ uint32_t step1(uint32_t q) const { return NBITS <= 3 ? q : (q ^ b) + 0x0c0c0c0cu; }
+  __device__ uint32_t step2(uint32_t x) const {
+    return NBITS <= 3 ? __builtin_amdgcn_perm(thi, tlo, x) : __builtin_amdgcn_perm(0u, 0u, x);
+  }
+  __device__ uint32_t step3(uint32_t x, uint32_t cs) const { return NBITS <= 3 ? cs & x : cs & ~x; }
+  __device__ uint32_t make(uint32_t q, uint32_t cs) const { return step3(step2(step1(q)), cs); }
+};
+
+// Balanced base-256 digits of four sums, lowest first, as words with one byte of each.
+__device__ inline void split_digits(const uint32_t (&z)[4], int4v (&w)[4], int vq, uint32_t bias = 0x00808080u) {
+  uint32_t y[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) y[u] = (z[u] + bias) ^ bias;
+  const uint32_t l01 = __builtin_amdgcn_perm(y[1], y[0], 0x05010400u), l23 = __builtin_amdgcn_perm(y[3], y[2], 0x05010400u);
+  const uint32_t h01 = __builtin_amdgcn_perm(y[1], y[0], 0x07030602u), h23 = __builtin_amdgcn_perm(y[3], y[2], 0x07030602u);
+  w[0][vq] = (int)__builtin_amdgcn_perm(l23, l01, 0x05040100u);
+  w[1][vq] = (int)__builtin_amdgcn_perm(l23, l01, 0x07060302u);
+  w[2][vq] = (int)__builtin_amdgcn_perm(h23, h01, 0x05040100u);
+  w[3][vq] = (int)__builtin_amdgcn_perm(h23, h01, 0x07060302u);
+}
+
+// D[d][v] = element (row (v>>2)*8 + kh*4 + (v&3), column l32) of digit d's fold: rows are (i', a), columns
+// (i'', b) of a column tile; i' == i'' is kept.  dst: this lane's column of M_i.
+template <int NBITS>
+__device__ inline void store_fold(const intx16 (&D)[4], float* __restrict__ dst, int l32, int kh, float weight, bool add) {
+  constexpr int C = 1 << NBITS;
+  float old[16];
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    const int row = (v >> 2) * 8 + kh * 4 + (v & 3);
+    old[v] = (add && (row >> NBITS) == (l32 >> NBITS)) ? dst[(row & (C - 1)) * C] : 0.f;
+  }
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    const int row = (v >> 2) * 8 + kh * 4 + (v & 3);
+    const float z = fmaf((float)(D[3][v] * 256 + D[2][v]), 65536.f, (float)(D[1][v] * 256 + D[0][v]));
+    if ((row >> NBITS) == (l32 >> NBITS)) dst[(row & (C - 1)) * C] = fmaf(z, weight, old[v]);
+  }
 }
 
 // All but the newest N of this wavefront's loads have arrived.
 template <int N>
 __device__ inline void wait_loads_but() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 
-// Asks the scheduler for the eight MFMAs of a half step with three vector operations behind each.
-__device__ inline void interleave() {
-#pragma unroll
-  for (int u = 0; u < 8; ++u) {
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-    __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);
-  }
-}
-
 // Workgroup = (slab of RW rows i, group g of row tiles {g, mtiles - 1 - g} of H): every
 // workgroup runs the same number of k-steps per digit, one barrier per k-step.
 //
-// The fold  M_i[a, b] += [Q_ij == a] 2^-s_j Z[j, (i, b)]  is an outer product per row j, and
-// v_mfma_f32_16x16x1_4b_f32 computes four independent 16 x 16 outer products per
-// instruction, one per group of 16 lanes.  In the 32 x 32 accumulator tile lane l holds
-// column l % 32 and register v holds one row j per lane half, so the 16-lane groups are
-// (lane half, 16-column half) and register v itself (converted to float) is the right
-// operand; the left operand is 2^-s_j where the code of (this lane's row i, that j) equals
-// l % C, else 0.  With C < 16 a 16-column group spans several rows i and only the diagonal
-// C x C blocks of the 16 x 16 result are meaningful; the others are never stored.
+// The fold  M_i[a, b] = sum_j [Q_ij == a] 2^-s_j Z[j, (i, b)]  is a product over j with another one-hot
+// operand.  In the 32 x 32 accumulator tile lane l holds column l % 32 in 16 rows j, which is how a lane of
+// the int8 MFMA supplies 16 k of its right operand: the sums are split into four balanced base-256 digits,
+// the left operand is 2^f_j where the code of (row i' of the column tile, that j) equals a (f_j = smax - s_j,
+// up to six; further apart: more rounds), and each digit takes one MFMA per 32 rows.  Exact until the
+// digits are put together.  Rows are (i', a), columns (i'', b); only the blocks i' == i'' are kept.
 template <int NBITS>
 __global__ __launch_bounds__(64 * TNW, 2) void t_accum_kernel(const int8_t* __restrict__ Hs,
                                                            const int8_t* __restrict__ Hd,
@@ -664,12 +741,15 @@ __global__ __launch_bounds__(64 * TNW, 2) void t_accum_kernel(const int8_t* __re
                                                            int64_t m_rows, int64_t n_cols,
                                                            int64_t npad, const uint8_t* __restrict__ Qp,
                                                            const uint8_t* __restrict__ Cs,
-                                                           const float* __restrict__ Wj,
-                                                           const int* __restrict__ Ptile,
+                                                           const uint8_t* __restrict__ Fj,
+                                                           const int8_t* __restrict__ S2,
+                                                           const int8_t* __restrict__ S3,
+                                                           const int* __restrict__ Ptile, int pair,
                                                            int64_t mpad, int mtiles, int ngroups,
                                                            float* __restrict__ Apart) {
-  // a sweep that updates A_i from the changed columns does not sum it again
-  if (t_use_delta(Tstat, m_rows, n_cols, fmax)) return;
+  // a sweep that updates A_i from the changed columns does not sum it again, nor does one that
+  // t_accum2_kernel sums
+  if ((pair != 0 && Tstat[5] != 0) || t_use_delta(Tstat, m_rows, n_cols, fmax)) return;
   constexpr int C = 1 << NBITS;
   constexpr int RW = TN >> NBITS;             // rows i per workgroup
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -684,8 +764,9 @@ __global__ __launch_bounds__(64 * TNW, 2) void t_accum_kernel(const int8_t* __re
   const int64_t qq = blockIdx.x >> 3;
   const int64_t item = (int64_t)(blockIdx.x & 7) * per + qq;
   if (qq >= per || item >= total) return;
-  const int group = (int)(item / nslabs);
-  const int64_t i0 = (item % nslabs) * RW;
+  // divisions are done on the vector unit; what they yield is the same in every lane
+  const int group = __builtin_amdgcn_readfirstlane((int)item / nslabs);
+  const int64_t i0 = (int64_t)((int)item - group * nslabs) * RW;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -696,18 +777,20 @@ __global__ __launch_bounds__(64 * TNW, 2) void t_accum_kernel(const int8_t* __re
   uint32_t qoff[2];
 #pragma unroll
   for (int jn = 0; jn < 2; ++jn) qoff[jn] = (uint32_t)(T_ATILEB + ((wave * 64 + jn * 32 + l32) >> NBITS) * TK + kh * 16);
-  const uint32_t coff = (uint32_t)(T_ATILEB + QS * 1024 + kh * 16);
-  const uint32_t bcode = (uint32_t)(lane & (C - 1)) * 0x01010101u;
-  // code loads: slot u < QS holds rows 16 u .. 16 u + 15 of the slab, slot QS the one-hot values (64
-  // bytes of it are used); further slots only even out the count
-  const int4v rsQ = make_rsrc(Qp + i0 * npad, (int64_t)RW * npad), rsC = make_rsrc(Cs, npad);
-  const uint32_t vq = (uint32_t)((lane >> 2) * npad + (lane & 3) * 16), vc = (uint32_t)(lane * 16);
+  const uint32_t coff = (uint32_t)(T_ATILEB + QS * 1024 + kh * 16), foff = (uint32_t)(T_ATILEB + (QS + 1) * 1024 + kh * 4);
+  const OneHotMaker<NBITS> maker(lane & (C - 1));
+  // code loads: slot u < QS holds rows 16 u .. 16 u + 15 of the slab, slot QS the one-hot values of the
+  // columns, slot QS + 1 the fold's factors of the rows of the same numbers (64 bytes each; the other
+  // lanes' offsets lie beyond any descriptor and move nothing); further slots only even out the count
+  constexpr uint32_t NOWHERE = 0x80000000u;
+  const int4v rsQ = make_rsrc(Qp + i0 * npad, (int64_t)RW * npad), rsC = make_rsrc(Cs, npad), rsF = make_rsrc(Fj, npad);
+  const uint32_t vq = (uint32_t)((lane >> 2) * npad + (lane & 3) * 16), vc = lane < TK / 16 ? (uint32_t)(lane * 16) : NOWHERE;
 
   // direct load of the A tile: one instruction covers 16 rows x 64 bytes; TM / 16 of them are
   // dealt to the wavefronts
   constexpr int ALD = (TM / 16) / TNW;
   const int dr = lane >> 2;
-  const int dc = (lane & 3) ^ ((dr >> 1) & 3);
+  const int dc = (lane & 3) ^ ((dr >> 2) & 3);
   uint32_t voff[ALD], voffd[ALD];      // in a row tile of Hs (row stride npad) and in a diagonal tile of Hd (TM)
 #pragma unroll
   for (int a = 0; a < ALD; ++a) {
@@ -715,7 +798,7 @@ __global__ __launch_bounds__(64 * TNW, 2) void t_accum_kernel(const int8_t* __re
     voffd[a] = (uint32_t)(((wave + TNW * a) * 16 + dr) * TM + dc * 16);
   }
 
-  const int rswz = (l32 >> 1) & 3;
+  const int rswz = (l32 >> 2) & 3;
   // per-lane LDS byte offset of the fragments inside a stage
   const int aoff = l32 * T_ROWB;
 
@@ -731,11 +814,12 @@ __global__ __launch_bounds__(64 * TNW, 2) void t_accum_kernel(const int8_t* __re
     struct Codes {
       int4v q[2], c;            // codes of the two column tiles and one-hot values of a half step
     };
-    auto load_codes = [&](Codes& d, int st, int ks) {
+    auto load_code = [&](Codes& d, int which, int st, int ks) {
       const unsigned char* S0 = smem + st * STAGEB + 32 * ks;
-      d.c = *reinterpret_cast<const int4v*>(S0 + coff);
-#pragma unroll
-      for (int jn = 0; jn < 2; ++jn) d.q[jn] = *reinterpret_cast<const int4v*>(S0 + qoff[jn]);
+      if (which < 2)
+        d.q[which] = *reinterpret_cast<const int4v*>(S0 + qoff[which]);
+      else
+        d.c = *reinterpret_cast<const int4v*>(S0 + coff);
     };
 
     intx16 acc[4][2];
@@ -749,32 +833,20 @@ __global__ __launch_bounds__(64 * TNW, 2) void t_accum_kernel(const int8_t* __re
     struct Frags {
       int4v a[4];
     };
-    auto load_frags = [&](Frags& f, int st, int ks) {
-      const unsigned char* S0 = smem + st * STAGEB;
-      const int cs = ((2 * ks + kh) ^ rswz) << 4;
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        f.a[i] = *reinterpret_cast<const int4v*>(S0 + aoff + i * 32 * T_ROWB + cs);
+    auto load_frag = [&](Frags& f, int i, int st, int ks) {
+      f.a[i] = *reinterpret_cast<const int4v*>(smem + st * STAGEB + aoff + i * 32 * T_ROWB + (((2 * ks + kh) ^ rswz) << 4));
     };
     struct OneHot {
-      int4v b[2];
+      int b[8];
     };
-    auto expand = [&](OneHot& o, const Codes& d) {
-#pragma unroll
-      for (int jn = 0; jn < 2; ++jn)
-#pragma unroll
-        for (int w = 0; w < 4; ++w)
-          o.b[jn][w] = (int)one_hot4((uint32_t)d.q[jn][w], bcode, (uint32_t)d.c[w]);
+    // the eight words of a one-hot operand, one operation of three of them per call
+    auto expand = [&](OneHot& o, const Codes& d, int x) {
+      auto at = [&](int w) -> int& { return reinterpret_cast<int&>(o.b[w]); };
+      if (x >= 2 && x < 10) at(x - 2) = (int)maker.step3((uint32_t)at(x - 2), (uint32_t)d.c[(x - 2) & 3]);
+      if (x >= 1 && x < 9) at(x - 1) = (int)maker.step2((uint32_t)at(x - 1));
+      if (x < 8) at(x) = (int)maker.step1((uint32_t)d.q[x >> 2][x & 3]);
     };
-    auto mma = [&](const Frags& f, const OneHot& o) {
-#pragma unroll
-      for (int jn = 0; jn < 2; ++jn)
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-          acc[i][jn] = __builtin_amdgcn_mfma_i32_32x32x32_i8(f.a[i], o.b[jn], acc[i][jn], 0, 0, 0);
-    };
-
-    const int acmp = lane & (C - 1);
+    auto operand = [&](const OneHot& o, int jn) { return int4v{o.b[4 * jn], o.b[4 * jn + 1], o.b[4 * jn + 2], o.b[4 * jn + 3]}; };
 
     for (int dg = 0; dg < P; ++dg) {
       int4v rsA, rsD;
@@ -790,28 +862,51 @@ __global__ __launch_bounds__(64 * TNW, 2) void t_accum_kernel(const int8_t* __re
         rsD[2] = (int)(uint32_t)(TM * TM);
         rsD[3] = 0x00020000;
       }
-      // the last two k-steps are the diagonal tile, whose copy in Hd is zero for k >= j
-      auto issue = [&](int k, int st) {
+      // The next request.  The last two k-steps are the diagonal tile, whose copy in Hd is zero for k >= j;
+      // requests past the last step move nothing, into a kilobyte behind the stages: the codes and factors
+      // of the diagonal tile stay for the fold.
+      constexpr int LPS = ALD + QL;
+      int4v prs = rsA;
+      int pk = 0;
+      uint32_t pstep = 1024, pv[LPS];       // each lane's offsets, advanced from step to step
 #pragma unroll
-        for (int u = 0; u < QL; ++u) {
-          const int slot = wave + TNW * u;
-          const uint32_t at = lds0 + st * STAGEB + T_ATILEB + slot * 1024;
-          if (slot < QS)
-            load16_to_lds(rsQ, at, vq, (uint32_t)(16 * slot * npad + (int64_t)k * TK));
-          else
-            load16_to_lds(rsC, at, vc, (uint32_t)k * (uint32_t)TK);
-        }
-        if (k < nk - TM / TK) {
+      for (int u = 0; u < LPS; ++u) {
+        const int slot = wave + TNW * (u - ALD);
+        pv[u] = u < ALD ? voff[u < ALD ? u : 0]
+                        : slot < QS ? vq + (uint32_t)(16 * slot * npad) : slot < QS + 2 ? vc : NOWHERE;
+      }
+      auto issue_source = [&]() {
+        if (pk == nk - TM / TK) {
+          prs = rsD;
 #pragma unroll
-          for (int a = 0; a < ALD; ++a)
-            load16_to_lds(rsA, lds0 + st * STAGEB + (wave + TNW * a) * 1024, voff[a], (uint32_t)k * (uint32_t)TK);
-        } else {
+          for (int u = 0; u < ALD; ++u) pv[u] = voffd[u];
+        } else if (pk == nk) {
+          pstep = 0;
 #pragma unroll
-          for (int a = 0; a < ALD; ++a)
-            load16_to_lds(rsD, lds0 + st * STAGEB + (wave + TNW * a) * 1024, voffd[a],
-                          (uint32_t)(k - (nk - TM / TK)) * (uint32_t)TK);
+          for (int u = 0; u < LPS; ++u) pv[u] = NOWHERE;
         }
       };
+      auto issue_one = [&](int st, int u) {
+        const uint32_t base = pstep != 0 ? lds0 + st * STAGEB : lds0 + NS * STAGEB;
+        if (u < ALD) {
+          load16_to_lds(prs, base + (wave + TNW * u) * pstep, pv[u], 0);
+        } else {
+          const int slot = wave + TNW * (u - ALD);
+          const uint32_t at = base + (T_ATILEB / 1024 + slot) * pstep;
+          if (slot < QS)
+            load16_to_lds(rsQ, at, pv[u], 0);
+          else if (slot == QS + 1)
+            load16_to_lds(rsF, at, pv[u], 0);
+          else
+            load16_to_lds(rsC, at, pv[u], 0);
+        }
+        pv[u] += TK;
+      };
+      auto issue_done = [&]() {
+        ++pk;
+        issue_source();
+      };
+      issue_source();
       if (dg > 0 && shared_acc) {
         // next digit: everything so far moves up by one digit
 #pragma unroll
@@ -823,114 +918,482 @@ __global__ __launch_bounds__(64 * TNW, 2) void t_accum_kernel(const int8_t* __re
       }
 
       // Every stage is free here (start of the kernel, or the barrier after the previous pass).
-      // Requests run NS - 1 stages ahead (past the last step they repeat it into a stage that is not
-      // read any more); the barrier at the top of step k publishes stage k + 1.
-      constexpr int LPS = ALD + QL;
+      // Requests run NS - 1 stages ahead; the barrier at the top of step k publishes stage k + 1.
 #pragma unroll
-      for (int u = 0; u < NS - 1; ++u) issue(u < nk ? u : nk - 1, u);
+      for (int s = 0; s < NS - 1; ++s)
+#pragma unroll
+        for (int u = 0; u < LPS; ++u) {
+          issue_one(s, u);
+          if (u == LPS - 1) issue_done();
+        }
       wait_loads_but<(NS - 2) * LPS>();
       __syncthreads();
       int st = 0, sn = NS - 1;
-      Frags f0, f1;
-      Codes c1, c2;
-      OneHot h0, h1;
-      load_codes(c2, 0, 0);
-      expand(h0, c2);
-      load_codes(c1, 0, 1);
-      load_frags(f0, 0, 0);
-      // One k-step of two halves: the operands of a half are read, and its one-hot operand is made,
-      // under the MFMAs of the half before (the codes one half earlier still).
+      Frags fr[2];
+      Codes cd[2];
+      OneHot oh[2];
+#pragma unroll
+      for (int w = 0; w < 3; ++w) load_code(cd[0], w, 0, 0);
+#pragma unroll
+      for (int w = 0; w < 3; ++w) load_code(cd[1], w, 0, 1);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) load_frag(fr[0], i, 0, 0);
+#pragma unroll
+      for (int x = 0; x < 10; ++x) expand(oh[0], cd[0], x);
+      // One k-step of two halves: the fragments of a half are read, and its one-hot operand is made, under
+      // the MFMAs of the half before (the codes one half earlier still).  The order is given: between two
+      // MFMAs stands what their 32 cycles hide, no vector operation next to the one it waits for, no two
+      // direct loads together.
 #pragma unroll 1
       for (int k = 0; k < nk; ++k) {
         const int st1 = (st == NS - 1) ? 0 : st + 1;
-        wait_loads_but<(NS - 3) * LPS>();
-        __syncthreads();
-        issue(k + NS - 1 < nk ? k + NS - 1 : nk - 1, sn);
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+          const int4v ob[2] = {operand(oh[ks], 0), operand(oh[ks], 1)};
+#pragma unroll
+          for (int g = 0; g < 8; ++g) {
+            acc[g >> 1][g & 1] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fr[ks].a[g >> 1], ob[g & 1], acc[g >> 1][g & 1], 0, 0, 0);
+            if (ks == 0 && g == 0) {
+              // publishes the next stage, and frees the one before
+              wait_loads_but<(NS - 3) * LPS>();
+              __syncthreads();
+            }
+            if (g < 4)
+              load_frag(fr[ks ^ 1], g, ks == 0 ? st : st1, ks ^ 1);
+            else if (g < 7)
+              load_code(cd[ks], g - 4, st1, ks);
+            if (g < 2) {
+              expand(oh[ks ^ 1], cd[ks ^ 1], 2 * g);
+              expand(oh[ks ^ 1], cd[ks ^ 1], 2 * g + 1);
+            } else {
+              expand(oh[ks ^ 1], cd[ks ^ 1], g + 2);
+            }
+            constexpr int GAP = 14 / LPS;
+            const int at = ks * 8 + g - 1;
+            if (at >= 0 && at % GAP == 0 && at / GAP < LPS) issue_one(sn, at / GAP);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        }
+        issue_done();
         sn = (sn == NS - 1) ? 0 : sn + 1;
-        load_frags(f1, st, 1);
-        load_codes(c2, st1, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        expand(h1, c1);
-        mma(f0, h0);
-        interleave();
-        __builtin_amdgcn_sched_barrier(0);
-        load_frags(f0, st1, 0);
-        load_codes(c1, st1, 1);
-        __builtin_amdgcn_sched_barrier(0);
-        expand(h0, c2);
-        mma(f1, h1);
-        interleave();
-        __builtin_amdgcn_sched_barrier(0);
         st = st1;
       }
       wait_all_loads();
-      // the LDS stages are reused by the next pass; slower wavefronts may still be reading
-      __syncthreads();
-      if (shared_acc && dg + 1 < P) continue;
+      if (shared_acc && dg + 1 < P) {
+        // the LDS stages are reused by the next pass; slower wavefronts may still be reading
+        __syncthreads();
+        continue;
+      }
 
-      // fold: register v of tile (i, jn) is row j = i*32 + (v>>2)*8 + kh*4 + (v&3) of the tile.
-      // D[jn] = four 16 x 16 blocks (lane half, column half) of column tile jn.  Accumulators
-      // that hold a single digit are folded with that digit's weight and start again from 0.
-      const float dgw = shared_acc ? 1.f : ldexpf(1.f, 8 * (P - 1 - dg));
+      // fold: register v of tile (i, jn) is row j = i*32 + (v>>2)*8 + kh*4 + (v&3) of the tile, its codes
+      // and factors are in the last two stages.  Accumulators that hold a single digit are folded with
+      // that digit's weight and start again from 0.
       const bool first_fold = half == 0 && (shared_acc || dg == 0);   // nothing stored yet
-      floatx16 D[2];
-#pragma unroll
-      for (int jn = 0; jn < 2; ++jn)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) D[jn][v] = 0.f;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        uint32_t qd[2][4];
-        float4 wj[4];
+      const int rounds = tile_rounds(tflags);
+      const int sb1 = (st == 0) ? NS - 1 : st - 1, sb0 = (sb1 == 0) ? NS - 1 : sb1 - 1;
+#pragma unroll 1
+      for (int p = 0; p < rounds; ++p) {
+        if (p > 0) {
+          // row scales more than 2^6 apart: the factors of the next round take the place of the last one's
+          __syncthreads();
+          if (tid < TM) {
+            const int64_t row = jt0 + tid;
+            smem[(tid < TK ? sb0 : sb1) * STAGEB + T_ATILEB + (QS + 1) * 1024 + (tid & (TK - 1))] =
+                row < n_cols ? fold_factor(tile_smax(tflags) - tile_exponent(P, S2[row], S3[row]), p) : 0;
+          }
+          __syncthreads();
+        }
+        uint32_t bias = 0x00808080u;
+        asm volatile("" : "+s"(bias));      // the digits are made anew in each round, not kept
+        const float weight = ldexpf(1.f, 7 * p - tile_smax(tflags) + (shared_acc ? 0 : 8 * (P - 1 - dg)));
 #pragma unroll
         for (int jn = 0; jn < 2; ++jn) {
-          const int il = (wave * 64 + jn * 32 + l32) >> NBITS;
-          const uint8_t* __restrict__ qr = Qp + (i0 + il) * npad + jt0 + i * 32 + kh * 4;
+          intx16 D[4];
 #pragma unroll
-          for (int vq = 0; vq < 4; ++vq) qd[jn][vq] = *reinterpret_cast<const uint32_t*>(qr + vq * 8);
-        }
+          for (int i = 0; i < 4; ++i) {
+            const unsigned char* S0 = smem + (i < 2 ? sb0 : sb1) * STAGEB;
+            int4v a, w[4];
 #pragma unroll
-        for (int vq = 0; vq < 4; ++vq) {
-          wj[vq] = *reinterpret_cast<const float4*>(Wj + jt0 + i * 32 + kh * 4 + vq * 8);
-          wj[vq].x *= dgw;
-          wj[vq].y *= dgw;
-          wj[vq].z *= dgw;
-          wj[vq].w *= dgw;
-        }
+            for (int vq = 0; vq < 4; ++vq) {
+              const int j = (i & 1) * 32 + vq * 8;      // of the stage, + kh * 4
+              const uint32_t q = *reinterpret_cast<const uint32_t*>(S0 + qoff[jn] - kh * 16 + kh * 4 + j);
+              const uint32_t f = *reinterpret_cast<const uint32_t*>(S0 + foff + j);
+              a[vq] = (int)maker.make(q, f);
+              uint32_t z[4];
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const float4 w4 = wj[v >> 2];
-          const float wv = (v & 3) == 0 ? w4.x : (v & 3) == 1 ? w4.y : (v & 3) == 2 ? w4.z : w4.w;
+              for (int u = 0; u < 4; ++u) z[u] = (uint32_t)acc[i][jn][4 * vq + u];
+              split_digits(z, w, vq, bias);
+            }
 #pragma unroll
-          for (int jn = 0; jn < 2; ++jn) {
-            const int code = (int)((qd[jn][v >> 2] >> (8 * (v & 3))) & 0xffu);
-            const float sel = (code == acmp) ? wv : 0.f;
-            D[jn] = __builtin_amdgcn_mfma_f32_16x16x1f32(sel, (float)acc[i][jn][v], D[jn], 0, 0, 0);
-            acc[i][jn][v] = 0;
+            for (int d = 0; d < 4; ++d)
+              D[d] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, w[d], i == 0 ? intx16{} : D[d], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
           }
+          // later folds add to what this same thread stored after the first
+          const int col = wave * 64 + jn * 32 + l32, il = col >> NBITS;
+          store_fold<NBITS>(D, Apart + ((int64_t)group * mpad + i0 + il) * C * C + (col & (C - 1)), l32, kh, weight,
+                            !first_fold || p > 0);
         }
       }
-      // D[jn][4 B + r] = block B = 2 * (lane half of the source) + (16-column half), element
-      // (row 4 (lane / 16) + r, column lane % 16): rows are (i', a), columns (i'', b) within the
-      // 16-column group; keep i' == i'' and add the two lane halves.  Later folds add to what this
-      // same thread stored after the first.
+      // the LDS stages are reused by the next pass; slower wavefronts may still be reading
+      __syncthreads();
 #pragma unroll
-      for (int jn = 0; jn < 2; ++jn)
+      for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int ch = 0; ch < 2; ++ch)
+        for (int jn = 0; jn < 2; ++jn)
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int mrow = 4 * (lane >> 4) + r, ncol = lane & 15;
-            if ((mrow >> NBITS) != (ncol >> NBITS)) continue;
-            float v = D[jn][4 * ch + r] + D[jn][4 * (2 + ch) + r];
-            const int col = wave * 64 + jn * 32 + ch * 16 + ncol;      // (row i, code b) pair of the slab
-            const int il = col >> NBITS, bb = col & (C - 1), aa = mrow & (C - 1);
-            float* dst = Apart + ((int64_t)group * mpad + i0 + il) * C * C + aa * C + bb;
-            if (!first_fold) v += *dst;
-            *dst = v;
-          }
+          for (int v = 0; v < 16; ++v) acc[i][jn][v] = 0;
     }
   }
+}
+
+// ---- the same for layers all of whose tiles have two digits that share one integer ----
+// Four wavefronts, one per SIMD and one workgroup per compute unit, each 128 rows j x 64 columns (i, b) in
+// both digits at once: 256 accumulator registers.  The digits share the one-hot operand and the staged
+// codes: 1.5 vector operations and 0.69 LDS reads per MFMA where a pass per digit takes 3 and 0.88, which
+// is energy, and energy is what bounds a long sum: at 8192 x 28672 the sweep takes 65.6 ms (70.8 with a pass
+// per digit), 4096 x 11008 5.9 ms (6.1).  A lone wavefront per SIMD has to do everything under its own MFMAs (2400
+// cycles a stage, 2048 of them MFMAs), so shorter sums gain less than the second launch costs (t_two_digits).
+// A workgroup takes its items one after the other, and a stage is requested NS - 1 stages ahead across tiles
+// and items, so that nothing drains at their ends.
+constexpr int TKS = 128;                     // k per stage: a row tile has one stage per tile left of it
+constexpr int D_ROWB = TKS;
+constexpr int D_ATILEB = TM * D_ROWB;
+constexpr int D_ASLOTS = 2 * D_ATILEB / 1024;
+constexpr int d_code_slots(int nbits) { return (TN >> nbits) * TKS / 1024; }
+// 1 KB loads per wavefront and stage: A, then the codes, one-hot values and fold factors
+constexpr int d_stage_loads(int nbits) { return (D_ASLOTS + d_code_slots(nbits) + 2 + TNW - 1) / TNW; }
+constexpr int d_stage_bytes(int nbits) { return d_stage_loads(nbits) * TNW * 1024; }
+constexpr int d_stages(int nbits) { return 4 * d_stage_bytes(nbits) <= 160 * 1024 ? 4 : 3; }
+
+template <int NBITS>
+__global__ __launch_bounds__(64 * TNW, 1) void t_accum2_kernel(const int8_t* __restrict__ Hs,
+                                                               const int8_t* __restrict__ Hd,
+                                                               const int* __restrict__ Tstat, int fmax,
+                                                               int64_t m_rows, int64_t n_cols,
+                                                               int64_t npad, const uint8_t* __restrict__ Qp,
+                                                               const uint8_t* __restrict__ Cs,
+                                                               const uint8_t* __restrict__ Fj,
+                                                               int64_t mpad, int mtiles, int ngroups,
+                                                               float* __restrict__ Apart) {
+  if (Tstat[5] == 0 || t_use_delta(Tstat, m_rows, n_cols, fmax)) return;
+  constexpr int C = 1 << NBITS;
+  constexpr int RW = TN >> NBITS;             // rows i per workgroup
+  constexpr int QS = d_code_slots(NBITS), LPS = d_stage_loads(NBITS), NS = d_stages(NBITS);
+  constexpr int LA = D_ASLOTS / TNW, LX = LPS - LA;         // loads of A, of the rest
+  constexpr int STAGEB = d_stage_bytes(NBITS);
+  constexpr int CODES = D_ASLOTS * 1024, VALUES = CODES + QS * 1024, FACTORS = VALUES + 1024;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)smem;
+
+  // Workgroups are dealt to the 8 XCDs round-robin by flat index; items are ordered (group, slab) and each
+  // XCD takes a contiguous eighth, which its workgroups walk side by side, so that those sharing an L2
+  // read the same rows of H.
+  const int nslabs = (int)(mpad / RW);
+  const int total = nslabs * ngroups;
+  const int per = (total + 7) / 8;
+  const int xcd = (int)(blockIdx.x & 7);
+  const int step = (int)(gridDim.x >> 3);
+  const int iend = (xcd + 1) * per < total ? (xcd + 1) * per : total;
+  const int ifirst = xcd * per + (int)(blockIdx.x >> 3);
+  if (ifirst >= iend) return;
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kh = lane >> 5, l32 = lane & 31;
+  constexpr uint32_t NOWHERE = 0x80000000u;      // beyond any descriptor: reads zero, moves nothing
+
+  // ---- the loads ----
+  // One load covers 8 rows x 128 bytes: lane -> row (lane / 8) and chunk position (lane % 8), which holds
+  // chunk position ^ ((row >> 1) & 7) of the row.
+  const int dr = lane >> 3, dc = (lane & 7) ^ (((wave & 1) << 2) | (dr >> 1));
+  const uint32_t voffH = (uint32_t)((wave * 8 + dr) * npad + dc * 16);       // A rows 8 (wave + 4 u) + dr of Hs
+  const uint32_t voffD = (uint32_t)((wave * 8 + dr) * TM + dc * 16);         // and of Hd
+  const uint32_t voffQ = (uint32_t)(dr * npad + dc * 16);                    // code rows 8 s + dr, s % 2 == wave % 2
+  // one-hot values and factors: 128 bytes; behind the factors lane 8 brings the tile's row exponent
+  const uint32_t voffC = lane < TKS / 16 ? (uint32_t)(lane * 16) : NOWHERE;
+  const uint32_t advance = lane == 8 ? 0 : TKS;
+
+  struct Tile {
+    int item, half, group, mt, i0;
+  };
+  auto set_tile = [&](Tile& t) {
+    t.mt = t.half == 0 ? t.group : mtiles - 1 - t.group;
+  };
+  auto set_item = [&](Tile& t, int item) {
+    t.item = item;
+    t.half = 0;
+    const int g = __builtin_amdgcn_readfirstlane(item / nslabs);
+    t.group = g;
+    t.i0 = (item - g * nslabs) * RW;
+    set_tile(t);
+  };
+  // false at the end of the workgroup's items
+  auto next_tile = [&](Tile& t) {
+    if (t.half == 0 && mtiles - 1 - t.group != t.group) {
+      t.half = 1;
+      set_tile(t);
+      return true;
+    }
+    if (t.item + step >= iend) return false;
+    set_item(t, t.item + step);
+    return true;
+  };
+  // the next request of this workgroup: step pk of tile pt, whose step pt.mt is the diagonal tile
+  Tile pt;
+  int pk = 0;
+  bool pdone = false;
+  uint32_t psoff = 0, prow = 0;                        // byte offset of the step in A; of 32 rows of A
+  uint32_t pvA, pvX[LX];                               // lane offsets of A; of codes, one-hot values, factors
+  int4v prs0, prs1, prsQ, prsL;                        // the last of the LX loads is of mixed kinds
+  auto set_source = [&]() {
+    const int64_t jt0 = (int64_t)pt.mt * TM;
+    psoff = 0;
+    if (pk != pt.mt) {
+      prs0 = make_rsrc(Hs + jt0 * npad, TM * npad);
+      prs1 = make_rsrc(Hs + (npad + jt0) * npad, TM * npad);
+      pvA = voffH;
+      prow = (uint32_t)(32 * npad);
+    } else {
+      // the diagonal tile's copy in Hd is zero for k >= j
+      prs0 = make_rsrc(Hd + jt0 * TM, TM * TM);
+      prs1 = make_rsrc(Hd + (npad + jt0) * TM, TM * TM);
+      pvA = voffD;
+      prow = 32 * TM;
+    }
+  };
+  auto start_tile = [&]() {
+    pk = 0;
+    prsQ = make_rsrc(Qp + (int64_t)pt.i0 * npad, (int64_t)RW * npad);
+    const int sl = wave + TNW * (LX - 1);
+    prsL = sl < QS ? prsQ : sl == QS ? make_rsrc(Cs, npad) : make_rsrc(Fj, npad + mtiles * 4 + 12);
+#pragma unroll
+    for (int x = 0; x < LX; ++x) {
+      const int s = wave + TNW * x;
+      pvX[x] = s < QS ? voffQ + (uint32_t)(8 * s * npad) : s < QS + 2 ? voffC : NOWHERE;
+      if (s == QS + 1 && lane == 8) pvX[x] = (uint32_t)(npad + pt.mt * 4);
+    }
+    set_source();
+  };
+  set_item(pt, ifirst);
+  start_tile();
+  Tile ct = pt;                                 // the tile that is being multiplied
+  // load u of the next stage's LPS, into stage st
+  auto issue_one = [&](int st, int u) {
+    const uint32_t at = lds0 + st * STAGEB + (wave + TNW * u) * 1024;
+    if (u < LA / 2)
+      load16_to_lds(prs0, at, pvA, psoff + u * prow);
+    else if (u < LA)
+      load16_to_lds(prs1, at, pvA, psoff + (u - LA / 2) * prow);
+    else
+      load16_to_lds(u < LPS - 1 ? prsQ : prsL, at, pvX[u - LA], 0);
+  };
+  auto issue_done = [&]() {
+    if (pdone) return;
+    ++pk;
+    psoff += TKS;
+#pragma unroll
+    for (int x = 0; x < LX - 1; ++x) pvX[x] += TKS;
+    pvX[LX - 1] += wave + TNW * (LX - 1) == QS + 1 ? advance : TKS;
+    if (pk < pt.mt) return;
+    if (pk == pt.mt) {
+      set_source();
+    } else if (next_tile(pt)) {
+      start_tile();
+    } else {
+      // nothing left: later requests move nothing, from addresses that exist
+      pdone = true;
+      psoff = 0;
+      pvA = NOWHERE;
+#pragma unroll
+      for (int x = 0; x < LX; ++x) pvX[x] = NOWHERE;
+    }
+  };
+
+  // ---- the operands ----
+  // this lane's columns (i, b) of the product: the codes of row i, 16 of every 32 k
+  const OneHotMaker<NBITS> maker(lane & (C - 1));
+  uint32_t qoff[2];
+  int qswz[2];
+#pragma unroll
+  for (int jn = 0; jn < 2; ++jn) {
+    const int il = (wave * 64 + jn * 32 + l32) >> NBITS;
+    qoff[jn] = (uint32_t)(CODES + il * TKS);
+    qswz[jn] = (il >> 1) & 7;
+  }
+  const int rswz = (l32 >> 1) & 7;
+  struct Codes {
+    int4v q[2], c;            // codes of the two column tiles and one-hot values of a quarter stage
+  };
+  struct Frags {
+    int4v a[2][4];
+  };
+  struct OneHot {
+    int b[8];
+  };
+  auto load_code = [&](Codes& d, int which, int st, int ks) {
+    const unsigned char* S0 = smem + st * STAGEB;
+    if (which < 2)
+      d.q[which] = *reinterpret_cast<const int4v*>(S0 + qoff[which] + (((2 * ks + kh) ^ qswz[which]) << 4));
+    else
+      d.c = *reinterpret_cast<const int4v*>(S0 + VALUES + 32 * ks + 16 * kh);
+  };
+  auto load_frag = [&](Frags& f, int d, int i, int st, int ks) {
+    f.a[d][i] = *reinterpret_cast<const int4v*>(smem + st * STAGEB + d * D_ATILEB + (i * 32 + l32) * D_ROWB +
+                                                (((2 * ks + kh) ^ rswz) << 4));
+  };
+  // the eight words of a one-hot operand, one operation of three of them per call
+  auto expand = [&](OneHot& o, const Codes& d, int x) {
+    if (x >= 2 && x < 10) o.b[x - 2] = (int)maker.step3((uint32_t)o.b[x - 2], (uint32_t)d.c[(x - 2) & 3]);
+    if (x >= 1 && x < 9) o.b[x - 1] = (int)maker.step2((uint32_t)o.b[x - 1]);
+    if (x < 8) o.b[x] = (int)maker.step1((uint32_t)d.q[x >> 2][x & 3]);
+  };
+
+  intx16 acc[2][4][2];
+  const intx16 zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+  Frags fr[2];
+  Codes cd[2];
+  OneHot oh[2];
+  int st = 0, sn = NS - 1;
+#pragma unroll
+  for (int s = 0; s < NS - 1; ++s) {
+#pragma unroll
+    for (int u = 0; u < LPS; ++u) issue_one(s, u);
+    issue_done();
+  }
+  wait_loads_but<(NS - 2) * LPS>();
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < 3; ++w) {
+    load_code(cd[0], w, 0, 0);
+    load_code(cd[1], w, 0, 1);
+  }
+#pragma unroll
+  for (int d = 0; d < 2; ++d)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) load_frag(fr[0], d, i, 0, 0);
+#pragma unroll
+  for (int x = 0; x < 10; ++x) expand(oh[0], cd[0], x);
+
+  // One stage in four quarters of 32 k.  The fragments of a quarter are read, and its one-hot operand is
+  // made, under the MFMAs of the quarter before (the codes one quarter earlier still).  The order is given:
+  // between two MFMAs stands what their 32 cycles hide, no vector operation next to the one it waits for.
+  auto stage = [&](auto first) {
+    const int st1 = (st == NS - 1) ? 0 : st + 1;
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      const Frags& f = fr[ks & 1];
+      const OneHot& o = oh[ks & 1];
+      const int4v ob[2] = {int4v{o.b[0], o.b[1], o.b[2], o.b[3]}, int4v{o.b[4], o.b[5], o.b[6], o.b[7]}};
+      Frags& fn = fr[(ks + 1) & 1];
+#pragma unroll
+      for (int g = 0; g < 16; ++g) {
+        const int d = g & 1, jn = (g >> 1) & 1, i = g >> 2;
+        acc[d][i][jn] = __builtin_amdgcn_mfma_i32_32x32x32_i8(f.a[d][i], ob[jn],
+                                                             (decltype(first)::value && ks == 0) ? zero : acc[d][i][jn], 0, 0, 0);
+        if (ks == 0 && g == 0) {
+          // publishes the next stage, and frees the one before
+          wait_loads_but<(NS - 3) * LPS>();
+          __syncthreads();
+        }
+        if (g < 8)
+          load_frag(fn, g & 1, g >> 1, ks < 3 ? st : st1, (ks + 1) & 3);
+        else if (g < 11)
+          load_code(cd[ks & 1], g - 8, ks < 2 ? st : st1, (ks + 2) & 3);
+        if (g < 10) expand(oh[(ks + 1) & 1], cd[(ks + 1) & 1], g);
+        constexpr int GAP = 60 / LPS;
+        const int at = ks * 16 + g - 2;
+        if (at >= 0 && at % GAP == 0 && at / GAP < LPS) issue_one(sn, at / GAP);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    issue_done();
+    sn = (sn == NS - 1) ? 0 : sn + 1;
+    st = st1;
+  };
+
+  // sums of an item: the registers whose rows can be this lane's i'
+  constexpr int SR = NBITS == 4 ? 8 : 4;
+  float S[2][SR];
+#pragma unroll
+  for (int jn = 0; jn < 2; ++jn)
+#pragma unroll
+    for (int x = 0; x < SR; ++x) S[jn][x] = 0.f;
+#pragma unroll 1
+  for (;;) {
+    const int last = (st + ct.mt) % NS;
+    stage(std::true_type{});
+#pragma unroll 1
+    for (int k = 0; k < ct.mt; ++k) stage(std::false_type{});
+    // the fold of t_accum_kernel; codes and factors of the rows are in the diagonal tile's stage
+    const unsigned char* S0 = smem + last * STAGEB;
+    const float weight = ldexpf(1.f, -*reinterpret_cast<const int*>(S0 + FACTORS + 128));
+    uint32_t fac[4][4], cod[2][4][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int vq = 0; vq < 4; ++vq) {
+        const int j = i * 32 + vq * 8 + kh * 4;
+        fac[i][vq] = *reinterpret_cast<const uint32_t*>(S0 + FACTORS + j);
+#pragma unroll
+        for (int jn = 0; jn < 2; ++jn)
+          cod[jn][i][vq] = *reinterpret_cast<const uint32_t*>(S0 + qoff[jn] + ((((i * 32 + vq * 8) >> 4) ^ qswz[jn]) << 4) + (j & 15));
+      }
+#pragma unroll
+    for (int jn = 0; jn < 2; ++jn) {
+      intx16 D[4];
+      int4v a[4], w[4][4];
+      auto prepare = [&](int i) {
+#pragma unroll
+        for (int vq = 0; vq < 4; ++vq) {
+          a[i][vq] = (int)maker.make(cod[jn][i][vq], fac[i][vq]);
+          uint32_t y[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) y[u] = (uint32_t)((acc[0][i][jn][4 * vq + u] << 8) + acc[1][i][jn][4 * vq + u]);
+          split_digits(y, w[i], vq);
+        }
+      };
+      // the sums of two row tiles leave their accumulators before D takes some
+      prepare(0);
+      prepare(1);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+#pragma unroll
+        for (int d = 0; d < 4; ++d) D[d] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[i], w[i][d], i == 0 ? zero : D[d], 0, 0, 0);
+        if (i < 2) prepare(i + 2);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      // of the 16 registers those whose rows are this lane's i': row (v>>2)*8 + kh*4 + (v&3), i' = row >> NBITS
+#pragma unroll
+      for (int x = 0; x < SR; ++x) {
+        float z = 0.f;
+#pragma unroll
+        for (int v = x; v < 16; v += SR) {
+          const float zv = fmaf((float)(D[3][v] * 256 + D[2][v]), 65536.f, (float)(D[1][v] * 256 + D[0][v]));
+          z = (v / SR == l32 >> (NBITS == 4 ? 4 : 3)) ? zv : z;
+        }
+        S[jn][x] = fmaf(z, weight, S[jn][x]);
+      }
+    }
+    const Tile was = ct;
+    const bool more = next_tile(ct);
+    if (more && ct.item == was.item) continue;
+#pragma unroll
+    for (int jn = 0; jn < 2; ++jn) {
+      const int col = wave * 64 + jn * 32 + l32, il = col >> NBITS;
+      float* __restrict__ dst = Apart + ((int64_t)(was.group * mpad + was.i0) + il) * C * C + (col & (C - 1));
+#pragma unroll
+      for (int x = 0; x < SR; ++x) {
+        const int row = (l32 >> (NBITS == 4 ? 4 : 3)) * SR + x;      // register
+        const int rr = (row >> 2) * 8 + kh * 4 + (row & 3);
+        if ((rr >> NBITS) == (l32 >> NBITS)) dst[(rr & (C - 1)) * C] = S[jn][x];
+        S[jn][x] = 0.f;
+      }
+    }
+    if (!more) break;
+  }
+  wait_all_loads();
 }
 
 // ---- per-row assembly and solve (one wavefront per row, float64) ----
@@ -1352,7 +1815,8 @@ hipError_t launch_t_prepare(hipStream_t s, const float* H, int64_t m, int64_t n,
   if (e != hipSuccess) return e;
   // the index j of a changed column is stored in 16 bits
   hipLaunchKernelGGL(t_symscale_kernel, dim3(1), dim3(1024), 0, s, sc.Ptile, (int)(npad / TM), n,
-                     (allow_delta != 0 && npad <= 65536) ? 1 : 0, sc.Cs, sc.S2, sc.Sneed, sc.Tstat);
+                     (allow_delta != 0 && npad <= 65536) ? 1 : 0, sc.Cs, sc.S2, sc.S3,
+                     npad, sc.Sneed, sc.Tstat);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(t_split_kernel, dim3((unsigned)ceil_div(npad, 256), (unsigned)npad), dim3(256), 0, s,
@@ -1386,6 +1850,13 @@ hipError_t launch_t_flips(hipStream_t s, int64_t m, int64_t n, int nbits, void* 
   return hipGetLastError();
 }
 
+// Whether a sweep may go to t_accum2_kernel (if all tiles suit it, which the device knows).  Its second launch
+// costs a sweep 5 us.  Pass per digit / both at once, us: many items 2048 x 2048 140 / 143, 4096 x 4096 902 /
+// 900 (3 bits 441 / 455, 2 bits 229 / 233), 4096 x 6144 1921 / 1880, 4096 x 11008 at 3 bits 2825 / 2774, 1024 x 16384
+// 3134 / 2870; no more items than compute units, where a lone workgroup has the unit to itself: 512 x 2048
+// 51 / 41, 256 x 4096 82 / 62, 512 x 1024 at 3 bits 32 / 27.
+inline bool t_two_digits(int64_t n, int64_t items) { return n >= 6144 || (items <= 256 && n >= 2048); }
+
 // partial M_i = sum_{j>k} [Q_ij = a][Q_ik = b] H_jk per group of row tiles (the one-hot GEMM)
 template <int NBITS>
 static hipError_t launch_t_accum_n(hipStream_t s, int64_t m, int64_t n, void* scratch, int cur) {
@@ -1394,16 +1865,24 @@ static hipError_t launch_t_accum_n(hipStream_t s, int64_t m, int64_t n, void* sc
   const int64_t npad = t_npad(n), mpad = t_mpad(m, NBITS);
   const int mtiles = (int)(npad / TM);
   const int groups = t_groups(n);
-  const int shmem = t_stages(NBITS) * t_stage_bytes(NBITS);
-  static std::atomic<uint64_t> lds_set{0};
-  {
-    const hipError_t ea = ensure_dynamic_lds((const void*)t_accum_kernel<NBITS>, shmem, lds_set);
-    if (ea != hipSuccess) return ea;
+  static std::atomic<uint64_t> lds_set{0}, lds_set2{0};
+  const int64_t items = (mpad / (TN >> NBITS)) * groups, wgs = 8 * ceil_div(items, 8);
+  const int pair = t_two_digits(n, items) ? 1 : 0;
+  hipError_t e;
+  if (pair) {
+    // this one or the next returns at once (Tstat[5]); one workgroup per compute unit walks its items
+    const int shmem = d_stages(NBITS) * d_stage_bytes(NBITS);
+    if ((e = ensure_dynamic_lds((const void*)t_accum2_kernel<NBITS>, shmem, lds_set2)) != hipSuccess) return e;
+    hipLaunchKernelGGL(t_accum2_kernel<NBITS>, dim3((unsigned)(wgs < 256 ? wgs : 256)), dim3(64 * TNW),
+                       shmem, s, sc.Hs, sc.Hd, sc.Tstat, sc.fmax, m, n, npad, sc.Qp[cur & 1], sc.Cs,
+                       (const uint8_t*)sc.Sneed, mpad, mtiles, groups, sc.Apart);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  const int64_t total = (mpad / (TN >> NBITS)) * groups;
-  hipLaunchKernelGGL(t_accum_kernel<NBITS>, dim3((unsigned)(8 * ceil_div(total, 8))), dim3(64 * TNW),
-                     shmem, s, sc.Hs, sc.Hd, sc.Tstat, sc.fmax, m, n, npad, sc.Qp[cur & 1], sc.Cs, sc.Wj,
-                     sc.Ptile, mpad, mtiles, groups, sc.Apart);
+  const int shmem = t_stages(NBITS) * t_stage_bytes(NBITS) + 1024;
+  if ((e = ensure_dynamic_lds((const void*)t_accum_kernel<NBITS>, shmem, lds_set)) != hipSuccess) return e;
+  hipLaunchKernelGGL(t_accum_kernel<NBITS>, dim3((unsigned)wgs), dim3(64 * TNW),
+                     shmem, s, sc.Hs, sc.Hd, sc.Tstat, sc.fmax, m, n, npad, sc.Qp[cur & 1], sc.Cs,
+                     (const uint8_t*)sc.Sneed, sc.S2, sc.S3, sc.Ptile, pair, mpad, mtiles, groups, sc.Apart);
   return hipGetLastError();
 }
 

@@ -1031,6 +1031,22 @@ def test_update_T_at_the_edges_of_slabs_and_stages(ctx, m, n, nbits):
     assert err.max() <= 1e-4, err.max()
 
 
+@pytest.mark.parametrize("m,n,nbits,kind", [(33, 2049, 4, "weak"), (16, 2176, 3, "weak"), (70, 2303, 2, "weak"),
+                                            (130, 2050, 1, "weak"), (20, 2100, 4, "wide"), (17, 6145, 4, "weak")])
+def test_update_T_both_digits_at_once(ctx, m, n, nbits, kind):
+    """Long sums go to a kernel that multiplies both digits of H in one pass, if every tile has two: odd and
+    even numbers of row tiles, more and less than one item per workgroup, row scales that differ within a
+    tile (several factors in the fold), and a matrix that needs more digits after all."""
+    H32 = _structured_H(kind, n, 31)
+    rng = np.random.default_rng(32)
+    W = (rng.standard_normal((m, n)) * 0.02).astype(np.float32)
+    Q = rng.integers(0, 1 << nbits, size=(m, n)).astype(np.uint8)
+    Tg = ctx.update_T(dev(W), dev(H32), dev(Q), dev(np.zeros((m, 1 << nbits), np.float32)), nbits).cpu().numpy()
+    Tref, _ = ref.update_T(W.astype(np.float64), H32.astype(np.float64), Q, nbits)
+    err = np.abs(Tg - Tref).max(axis=1) / np.abs(Tref).max(axis=1)
+    assert err.max() <= 1e-4, err.max()
+
+
 @pytest.mark.parametrize("n,events", [(130, (100,)), (1000, (990, 500)), (2200, (2150, 1500, 700))])
 def test_update_S_infinite_and_nan_weights(ctx, n, events):
     """An infinite weight makes an infinite residual whatever its code, and with it every target further
