@@ -6,7 +6,7 @@
 // token axis is split across workgroups so that small n still fills the chip,
 // each split writes its partial tile to scratch, and a second kernel sums the
 // partials in a fixed order (bit-reproducible, no float atomics) and writes
-// both triangles of H.
+// both triangles of H.  A product that is not split writes them itself.
 //
 // Operand tiles go from global memory straight into LDS (buffer_load ... lds): no
 // registers are held across the MFMA block and no LDS store instructions are issued.  Such
@@ -133,7 +133,8 @@ template <bool TOK>
 __global__ __launch_bounds__(64 * HNW) void hessian_f16_kernel(const _Float16* __restrict__ X, int64_t n,
                                                               int64_t p, int64_t ldx, int64_t chunk,
                                                               int nt, int ntiles, int ngroups, int gsz,
-                                                              int nsplit, float* __restrict__ partials) {
+                                                              int nsplit, float* __restrict__ partials,
+                                                              float* __restrict__ H, int64_t ldh, int accumulate) {
   // Workgroups are dealt to the 8 XCDs round-robin by their flat index, so the 32 workgroups
   // with consecutive (blockIdx.x >> 3) run side by side on one XCD.  They take one group of at
   // most 32 tiles of one token split, and the groups are runs of the Z-order of the triangle:
@@ -338,6 +339,72 @@ __global__ __launch_bounds__(64 * HNW) void hessian_f16_kernel(const _Float16* _
     }
   }
 
+  if (nsplit == 1) {
+    // The tile's sums are complete and go to both triangles of H from here: 8 calls of 2048 tokens at n =
+    // 4096 took 66 + 26 us each with the second kernel, now 76.  What H held is requested three 32 x 32 tiles
+    // ahead (one tile at a time the loads alone take 25 us), and the mirrored elements are turned in a piece
+    // of LDS of the wavefront's own, so that they leave as whole lines (16-byte runs straight from the
+    // registers, or single elements in the tiles on the diagonal: 102 to 110 us).
+    const bool vec = (ldh % 4) == 0 && (((uintptr_t)H) & 15) == 0;
+    __syncthreads();          // nobody reads the stages any more
+    constexpr int TLD = 36;   // floats per row of the piece
+    float* piece = reinterpret_cast<float*>(hsm) + wave * (32 * TLD);
+    const int64_t r0 = m0 + wr * 128, c0 = n0 + wc * 64;
+    float* __restrict__ low = H + (r0 + kh * 4) * ldh + c0 + l32;
+    float* __restrict__ up = H + (c0 + (lane >> 3)) * ldh + r0 + (lane & 7) * 4;
+    // 32 x 32 tile t: nothing to do right of the diagonal; whole ones need no test per element
+    auto empty = [&](int t) { return c0 + (t & 1) * 32 > r0 + (t >> 1) * 32 || r0 + (t >> 1) * 32 >= n; };
+    auto whole = [&](int t) { return vec && c0 + (t & 1) * 32 < r0 + (t >> 1) * 32 && r0 + (t >> 1) * 32 + 32 <= n; };
+    auto keep = [&](int t, int v) {
+      const int64_t row = r0 + (t >> 1) * 32 + kh * 4 + (v >> 2) * 8 + (v & 3);
+      return row < n && c0 + (t & 1) * 32 + l32 <= row;
+    };
+    float old[8][16];
+    auto request = [&](int t) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) old[t][v] = 0.f;
+      if (accumulate && !empty(t)) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+          if (whole(t) || keep(t, v)) old[t][v] = low[((t >> 1) * 32 + (v >> 2) * 8 + (v & 3)) * ldh + (t & 1) * 32];
+      }
+    };
+    request(0);
+    request(1);
+    request(2);
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      if (t + 3 < 8) request(t + 3);
+      if (empty(t)) continue;
+      floatx16& a = acc[t >> 1][t & 1];
+      const bool all = whole(t);
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        a[v] += old[t][v];
+        if (all || keep(t, v)) low[((t >> 1) * 32 + (v >> 2) * 8 + (v & 3)) * ldh + (t & 1) * 32] = a[v];
+      }
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4)
+        *reinterpret_cast<floatx4*>(piece + l32 * TLD + q4 * 8 + kh * 4) =
+            floatx4{a[4 * q4], a[4 * q4 + 1], a[4 * q4 + 2], a[4 * q4 + 3]};
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const floatx4 x = *reinterpret_cast<const floatx4*>(piece + (c * 8 + (lane >> 3)) * TLD + (lane & 7) * 4);
+        float* __restrict__ d = up + ((t & 1) * 32 + c * 8) * ldh + (t >> 1) * 32;
+        if (all) {
+          *reinterpret_cast<floatx4*>(d) = x;
+        } else {
+          const int64_t col = c0 + (t & 1) * 32 + c * 8 + (lane >> 3), row = r0 + (t >> 1) * 32 + (lane & 7) * 4;
+#pragma unroll
+          for (int u = 0; u < 4; ++u)
+            if (row + u < n && col < row + u) d[u] = x[u];
+        }
+      }
+      __builtin_amdgcn_wave_barrier();
+    }
+    return;
+  }
   float* out = partials + (int64_t)split * n * n;
 #pragma unroll
   for (int i = 0; i < 4; ++i)
@@ -461,9 +528,9 @@ hipError_t launch_hessian_f16(hipStream_t s, const _Float16* X, int64_t n, int64
     if (ea != hipSuccess) return ea;
   }
   hipLaunchKernelGGL(hessian_f16_kernel<false>, grid, dim3(64 * HNW), hs(false) * hstageb(false), s, X, n, p, ldx, chunk,
-                     (int)nt, ntiles, ngroups, gsz, split, partials);
+                     (int)nt, ntiles, ngroups, gsz, split, partials, H, ldh, accumulate);
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  if (e != hipSuccess || split == 1) return e;
   dim3 g2((unsigned)ceil_div(n, 32), (unsigned)ceil_div(n, 32));
   hipLaunchKernelGGL(reduce_mirror_kernel, g2, dim3(256), 0, s, H, n, ldh, partials, n, split,
                      accumulate);
@@ -496,9 +563,9 @@ hipError_t launch_hessian_f16_tokens(hipStream_t s, const _Float16* Xt, int64_t 
     if (ea != hipSuccess) return ea;
   }
   hipLaunchKernelGGL(hessian_f16_kernel<true>, grid, dim3(64 * HNW), hs(true) * hstageb(true), s, Xt, n, p, ldxt, chunk,
-                     (int)nt, ntiles, ngroups, gsz, split, partials);
+                     (int)nt, ntiles, ngroups, gsz, split, partials, H, ldh, accumulate);
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  if (e != hipSuccess || split == 1) return e;
   dim3 g2((unsigned)ceil_div(n, 32), (unsigned)ceil_div(n, 32));
   hipLaunchKernelGGL(reduce_mirror_kernel, g2, dim3(256), 0, s, H, n, ldh, partials, n, split,
                      accumulate);

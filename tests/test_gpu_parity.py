@@ -992,6 +992,29 @@ def test_hessian_fp32_token_splits(ctx, n, p):
     assert np.all(np.abs(H2 - 2 * Href) <= 2 * tol) and np.array_equal(H2, H2.T)
 
 
+@pytest.mark.parametrize("n", [31, 255, 256, 257, 530, 800])
+@pytest.mark.parametrize("pad", [0, 1, 4])
+@pytest.mark.parametrize("tokens", [False, True])
+def test_hessian_unsplit_product_writes_both_triangles(ctx, n, pad, tokens):
+    """A product whose tokens are not split writes H itself: tiles on the diagonal, at the edge and whole
+    ones, rows that start on 16 bytes and not, added to what the lower triangle held.  X holds small whole
+    numbers, so every sum is exact."""
+    p = 136
+    g = torch.Generator().manual_seed(n + pad)
+    X = torch.randint(-3, 4, (n, p), generator=g)
+    want = (X.double() @ X.double().t())
+    Xg = (X.t().contiguous() if tokens else X).half().cuda()
+    build = ctx.build_hessian_tokens if tokens else ctx.build_hessian
+    big = torch.full((n + 2, n + pad), 7.0, device="cuda")
+    H = big[:n, :n]
+    build(Xg, H=H)
+    assert torch.equal(H.cpu().double(), want)
+    H.add_(torch.triu(torch.ones(n, n, device="cuda"), 1))           # what the upper triangle held is not read
+    build(Xg, H=H, accumulate=True)
+    assert torch.equal(H.cpu().double(), 2 * want)
+    assert bool((big[n:] == 7.0).all()) and bool((big[:, n:] == 7.0).all())
+
+
 @pytest.mark.parametrize("n", [4353, 4480, 4607])
 def test_cholesky_trailing_updates_on_the_fp16_units(ctx, n):
     """The first trailing update of these sizes (more than 4096 rows below the panel; whole tiles, ragged
