@@ -726,7 +726,8 @@ template <int N>
 __device__ inline void wait_loads_but() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 
 // Workgroup = (slab of RW rows i, group g of row tiles {g, mtiles - 1 - g} of H): every
-// workgroup runs the same number of k-steps per digit, one barrier per k-step.
+// workgroup runs the same number of k-steps per digit, one barrier per k-step.  Where that leaves most of
+// the chip idle each digit (digits dg = slot, slot + ds, ..) has a workgroup and partial sums of its own.
 //
 // The fold  M_i[a, b] = sum_j [Q_ij == a] 2^-s_j Z[j, (i, b)]  is a product over j with another one-hot
 // operand.  In the 32 x 32 accumulator tile lane l holds column l % 32 in 16 rows j, which is how a lane of
@@ -744,7 +745,7 @@ __global__ __launch_bounds__(64 * TNW, 2) void t_accum_kernel(const int8_t* __re
                                                            const uint8_t* __restrict__ Fj,
                                                            const int8_t* __restrict__ S2,
                                                            const int8_t* __restrict__ S3,
-                                                           const int* __restrict__ Ptile, int pair,
+                                                           const int* __restrict__ Ptile, int pair, int ds,
                                                            int64_t mpad, int mtiles, int ngroups,
                                                            float* __restrict__ Apart) {
   // a sweep that updates A_i from the changed columns does not sum it again, nor does one that
@@ -765,8 +766,9 @@ __global__ __launch_bounds__(64 * TNW, 2) void t_accum_kernel(const int8_t* __re
   const int64_t item = (int64_t)(blockIdx.x & 7) * per + qq;
   if (qq >= per || item >= total) return;
   // divisions are done on the vector unit; what they yield is the same in every lane
-  const int group = __builtin_amdgcn_readfirstlane((int)item / nslabs);
-  const int64_t i0 = (int64_t)((int)item - group * nslabs) * RW;
+  const int part = __builtin_amdgcn_readfirstlane((int)item / nslabs);
+  const int group = __builtin_amdgcn_readfirstlane(part / ds), slot = part - group * ds;
+  const int64_t i0 = (int64_t)((int)item - part * nslabs) * RW;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -802,6 +804,7 @@ __global__ __launch_bounds__(64 * TNW, 2) void t_accum_kernel(const int8_t* __re
   // per-lane LDS byte offset of the fragments inside a stage
   const int aoff = l32 * T_ROWB;
 
+  bool stored = false;
   for (int half = 0; half < 2; ++half) {
     const int mt = (half == 0) ? group : mtiles - 1 - group;
     if (half == 1 && mt == group) break;
@@ -809,7 +812,7 @@ __global__ __launch_bounds__(64 * TNW, 2) void t_accum_kernel(const int8_t* __re
     const int nk = (int)((jt0 + TM) / TK);    // tiles right of the diagonal are never needed (nk >= 2)
     const int tflags = __builtin_amdgcn_readfirstlane(Ptile[mt]);
     const int P = tile_digits(tflags);
-    const bool shared_acc = tile_shared_acc(tflags);   // the digits may share the accumulators
+    const bool shared_acc = ds == 1 && tile_shared_acc(tflags);   // the digits may share the accumulators
 
     struct Codes {
       int4v q[2], c;            // codes of the two column tiles and one-hot values of a half step
@@ -848,7 +851,7 @@ __global__ __launch_bounds__(64 * TNW, 2) void t_accum_kernel(const int8_t* __re
     };
     auto operand = [&](const OneHot& o, int jn) { return int4v{o.b[4 * jn], o.b[4 * jn + 1], o.b[4 * jn + 2], o.b[4 * jn + 3]}; };
 
-    for (int dg = 0; dg < P; ++dg) {
+    for (int dg = slot; dg < P; dg += ds) {
       int4v rsA, rsD;
       {
         const uint64_t ad = (uint64_t)(uintptr_t)(Hs + ((int64_t)dg * npad + jt0) * npad);
@@ -988,7 +991,6 @@ __global__ __launch_bounds__(64 * TNW, 2) void t_accum_kernel(const int8_t* __re
       // fold: register v of tile (i, jn) is row j = i*32 + (v>>2)*8 + kh*4 + (v&3) of the tile, its codes
       // and factors are in the last two stages.  Accumulators that hold a single digit are folded with
       // that digit's weight and start again from 0.
-      const bool first_fold = half == 0 && (shared_acc || dg == 0);   // nothing stored yet
       const int rounds = tile_rounds(tflags);
       const int sb1 = (st == 0) ? NS - 1 : st - 1, sb0 = (sb1 == 0) ? NS - 1 : sb1 - 1;
 #pragma unroll 1
@@ -1031,10 +1033,11 @@ __global__ __launch_bounds__(64 * TNW, 2) void t_accum_kernel(const int8_t* __re
           }
           // later folds add to what this same thread stored after the first
           const int col = wave * 64 + jn * 32 + l32, il = col >> NBITS;
-          store_fold<NBITS>(D, Apart + ((int64_t)group * mpad + i0 + il) * C * C + (col & (C - 1)), l32, kh, weight,
-                            !first_fold || p > 0);
+          store_fold<NBITS>(D, Apart + ((int64_t)part * mpad + i0 + il) * C * C + (col & (C - 1)), l32, kh, weight,
+                            stored || p > 0);
         }
       }
+      stored = true;
       // the LDS stages are reused by the next pass; slower wavefronts may still be reading
       __syncthreads();
 #pragma unroll
@@ -1045,6 +1048,9 @@ __global__ __launch_bounds__(64 * TNW, 2) void t_accum_kernel(const int8_t* __re
           for (int v = 0; v < 16; ++v) acc[i][jn][v] = 0;
     }
   }
+  // a part whose tiles have fewer digits adds nothing
+  if (!stored)
+    for (int64_t e = tid; e < (int64_t)RW * C * C; e += 64 * TNW) Apart[((int64_t)part * mpad + i0) * C * C + e] = 0.f;
 }
 
 // ---- the same for layers all of whose tiles have two digits that share one integer ----
@@ -1702,6 +1708,21 @@ inline int64_t t_npad(int64_t n) { return ceil_div(n, TM) * TM; }
 inline int64_t t_mpad(int64_t m, int nbits) { const int64_t rw = TN >> nbits; return ceil_div(m, rw) * rw; }
 inline int t_groups(int64_t n) { return (int)((ceil_div(n, TM) + 1) / 2); }
 
+// Whether a sweep may go to t_accum2_kernel (if all tiles suit it, which the device knows).  Its second launch
+// costs a sweep 5 us.  Pass per digit / both at once, us: many items 2048 x 2048 140 / 143, 4096 x 4096 902 /
+// 900 (3 bits 441 / 455, 2 bits 229 / 233), 4096 x 6144 1921 / 1880, 4096 x 11008 at 3 bits 2825 / 2774, 1024 x 16384
+// 3134 / 2870; no more items than compute units, where a lone workgroup has the unit to itself: 512 x 2048
+// 51 / 41, 256 x 4096 82 / 62, 512 x 1024 at 3 bits 32 / 27.
+inline bool t_two_digits(int64_t n, int64_t items) { return n >= 6144 || (items <= 256 && n >= 2048); }
+
+// Workgroups per item: as many, up to one per digit, as the chip takes at once (two per compute unit) and the
+// scratch holds partial sums for.  256 x 512 (32 items, three digits) 41 -> 17 us.
+inline int t_digit_split(int64_t n, int64_t items, int64_t room) {
+  int ds = t_two_digits(n, items) ? 1 : TP;
+  while (ds > 1 && (items * ds > 512 || ds > room)) --ds;
+  return ds;
+}
+
 struct TScratch {
   float* scale;
   float* Hdiag;
@@ -1725,6 +1746,7 @@ struct TScratch {
   double* Dpart;        // one C x C slot per chunk of changed columns
   int64_t max_chunks;
   int fmax;
+  int ds;               // workgroups per item of t_accum_kernel, one or more digits each
 };
 
 // most changed columns per row that a sweep may update instead of summing A_i again
@@ -1752,9 +1774,7 @@ inline size_t t_layout(int64_t m, int64_t n, int nbits, char* base, TScratch* ou
   const size_t o_hd = take((size_t)TP * npad * TM);
   const size_t o_q = take((size_t)mpad * npad);
   const size_t o_q2 = take((size_t)mpad * npad);
-  const size_t o_ap = take((size_t)t_groups(n) * mpad * C * C * sizeof(float));
   const int fmax = t_fmax(npad);
-  const size_t o_fl = take((size_t)mpad * fmax * sizeof(uint32_t));
   const size_t o_fc = take((size_t)mpad * sizeof(int));
   const size_t o_ts = take((8 + 3 * kTLogMax) * sizeof(int));   // counters, then (choice, max, total) per sweep
   const size_t o_as = take((size_t)mpad * C * C * sizeof(double));
@@ -1763,8 +1783,14 @@ inline size_t t_layout(int64_t m, int64_t n, int nbits, char* base, TScratch* ou
   const size_t o_cb = take((size_t)(mpad + 1) * sizeof(int));
   // a sweep is updated only when at most m n / kDeltaInv indices changed
   const int64_t max_chunks = (m * n / kDeltaInv) / kDeltaChunk + m + 1;
+  // the partial sums of a sweep that splits its digits go on over the two areas that only a sweep that
+  // updates needs
+  const size_t part = (size_t)mpad * C * C * sizeof(float);
+  const size_t o_ap = take((size_t)t_groups(n) * part);
+  const size_t o_fl = take((size_t)mpad * fmax * sizeof(uint32_t));
   const size_t o_dp = take((size_t)max_chunks * C * C * sizeof(double));
   if (out != nullptr) {
+    out->ds = t_digit_split(n, mpad / (TN >> nbits) * t_groups(n), (int64_t)((off - o_ap) / part) / t_groups(n));
     out->scale = (float*)(base + o_scale);
     out->Hdiag = (float*)(base + o_diag);
     out->Cs = (uint8_t*)(base + o_cs);
@@ -1850,13 +1876,6 @@ hipError_t launch_t_flips(hipStream_t s, int64_t m, int64_t n, int nbits, void* 
   return hipGetLastError();
 }
 
-// Whether a sweep may go to t_accum2_kernel (if all tiles suit it, which the device knows).  Its second launch
-// costs a sweep 5 us.  Pass per digit / both at once, us: many items 2048 x 2048 140 / 143, 4096 x 4096 902 /
-// 900 (3 bits 441 / 455, 2 bits 229 / 233), 4096 x 6144 1921 / 1880, 4096 x 11008 at 3 bits 2825 / 2774, 1024 x 16384
-// 3134 / 2870; no more items than compute units, where a lone workgroup has the unit to itself: 512 x 2048
-// 51 / 41, 256 x 4096 82 / 62, 512 x 1024 at 3 bits 32 / 27.
-inline bool t_two_digits(int64_t n, int64_t items) { return n >= 6144 || (items <= 256 && n >= 2048); }
-
 // partial M_i = sum_{j>k} [Q_ij = a][Q_ik = b] H_jk per group of row tiles (the one-hot GEMM)
 template <int NBITS>
 static hipError_t launch_t_accum_n(hipStream_t s, int64_t m, int64_t n, void* scratch, int cur) {
@@ -1866,7 +1885,7 @@ static hipError_t launch_t_accum_n(hipStream_t s, int64_t m, int64_t n, void* sc
   const int mtiles = (int)(npad / TM);
   const int groups = t_groups(n);
   static std::atomic<uint64_t> lds_set{0}, lds_set2{0};
-  const int64_t items = (mpad / (TN >> NBITS)) * groups, wgs = 8 * ceil_div(items, 8);
+  const int64_t items = (mpad / (TN >> NBITS)) * groups, wgs = 8 * ceil_div(items * sc.ds, 8);
   const int pair = t_two_digits(n, items) ? 1 : 0;
   hipError_t e;
   if (pair) {
@@ -1882,7 +1901,7 @@ static hipError_t launch_t_accum_n(hipStream_t s, int64_t m, int64_t n, void* sc
   if ((e = ensure_dynamic_lds((const void*)t_accum_kernel<NBITS>, shmem, lds_set)) != hipSuccess) return e;
   hipLaunchKernelGGL(t_accum_kernel<NBITS>, dim3((unsigned)wgs), dim3(64 * TNW),
                      shmem, s, sc.Hs, sc.Hd, sc.Tstat, sc.fmax, m, n, npad, sc.Qp[cur & 1], sc.Cs,
-                     (const uint8_t*)sc.Sneed, sc.S2, sc.S3, sc.Ptile, pair, mpad, mtiles, groups, sc.Apart);
+                     (const uint8_t*)sc.Sneed, sc.S2, sc.S3, sc.Ptile, pair, sc.ds, mpad, mtiles, groups * sc.ds, sc.Apart);
   return hipGetLastError();
 }
 
@@ -1924,7 +1943,7 @@ hipError_t launch_t_solve(hipStream_t s, const float* G, int64_t ldg, int64_t m,
   t_layout(m, n, nbits, (char*)scratch, &sc);
   const int64_t mpad = t_mpad(m, nbits);
   int* tlog = (sweep >= 0 && sweep < kTLogMax) ? sc.Tstat + 8 + 3 * sweep : nullptr;
-  hipLaunchKernelGGL(t_solve_kernel, dim3((unsigned)m), dim3(64), 0, s, sc.Apart, t_groups(n), sc.Tstat, sc.fmax,
+  hipLaunchKernelGGL(t_solve_kernel, dim3((unsigned)m), dim3(64), 0, s, sc.Apart, t_groups(n) * sc.ds, sc.Tstat, sc.fmax,
                      m, sc.Astate, tlog, sc.Cbase, sc.Dpart, sc.Vstate, sc.Nstate, sc.Flist, sc.Fcnt, mpad, sc.scale,
                      sc.Hdiag, G, ldg, Q, ldq, n, nbits,
                      empty_mode, T, empty_count);
