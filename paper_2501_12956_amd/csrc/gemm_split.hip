@@ -120,7 +120,7 @@ __global__ __launch_bounds__(TILE * 2, 2) void pair_gemm_kernel(const _Float16* 
   const int64_t rowsB = (N - n0 < TILE) ? N - n0 : TILE;
 
   // lane -> (row of 8, 16-byte chunk): chunk c of row r sits at position c ^ (r & 7)
-  const int dr = lane >> 3, dc = (lane & 7) ^ dr;
+  const int dr = lane >> 3, dc = (lane & 7) ^ (((wave & 1) << 2) | (dr >> 1));
   uint32_t voff[DPW];
 #pragma unroll
   for (int j = 0; j < DPW; ++j) voff[j] = (uint32_t)(((int64_t)((wave + NWV * j) * 8 + dr) * ldp + dc * 8) * 2);
@@ -153,7 +153,7 @@ __global__ __launch_bounds__(TILE * 2, 2) void pair_gemm_kernel(const _Float16* 
         if constexpr (TWO) crs[i][j][v] = tot[i][j][v] = 0.f;
       }
 
-  const int rswz = l32 & 7;
+  const int rswz = (l32 >> 1) & 7;
   if (sb < se) issue(sb, 0);
   int st = 0;
 #pragma unroll 1
@@ -296,7 +296,7 @@ __global__ __launch_bounds__(256, 2) void pair_syrk256_kernel(const _Float16* __
   const int kh = lane >> 5, l32 = lane & 31;
   const int64_t m0 = (int64_t)bm * TILE, n0 = (int64_t)bn * TILE;
   const int64_t rowsA = (M - m0 < TILE) ? M - m0 : TILE, rowsB = (M - n0 < TILE) ? M - n0 : TILE;
-  const int dr = lane >> 3, dc = (lane & 7) ^ dr;
+  const int dr = lane >> 3, dc = (lane & 7) ^ (((wave & 1) << 2) | (dr >> 1));
   uint32_t voff[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) voff[j] = (uint32_t)((((wave + 4 * j) * 8 + dr) * LDP + dc * 8) * 2);
@@ -318,7 +318,7 @@ __global__ __launch_bounds__(256, 2) void pair_syrk256_kernel(const _Float16* __
     for (int j = 0; j < 2; ++j)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = crs[i][j][v] = 0.f;
-  const int rswz = l32 & 7;
+  const int rswz = (l32 >> 1) & 7;
 #pragma unroll 1
   for (int s = 0; s < STEPS; ++s) {
     wait_all_loads();
