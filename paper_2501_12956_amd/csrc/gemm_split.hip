@@ -15,6 +15,8 @@
 // the H = X X^T kernel's skeleton otherwise: 8 wavefronts of 128 x 64, tiles loaded straight into
 // LDS (buffer_load ... lds) with XOR-permuted 16-byte chunks, two stages, one barrier per step;
 // small tiles are 4 wavefronts of 64 x 64, two workgroups per compute unit.
+// The reads of a step are spread over its MFMAs, each row of 16 lanes in banks of its own: the S-update's
+// products of an 8192 x 28672 sweep 19.0 -> 18.5 ms, large tiles 35.4 -> 35.2 (power takes the rest).
 // Bound by MFMA issue and power at large sizes: 8192 x 28672 x 28672 38.3 -> 32.0 ms (1.26 PFLOP/s
 // issued, what a large bf16 library product reaches on the same card), 4096^3 365 -> 320 us,
 // 2048^3 141 -> 66 us; making the pieces 26 + 10 -> 7 us per 2048 x 2048 operand (a row's exponent
@@ -80,6 +82,18 @@ __global__ __launch_bounds__(256) void pair_split_kernel(const float* __restrict
   }
 }
 
+// Asks the scheduler for the reads of a step (RD of them, the first AHEAD in front) spread over its MF MFMAs.
+template <int RD, int AHEAD, int MF>
+__device__ inline void spread_reads() {
+  __builtin_amdgcn_sched_group_barrier(0x100, AHEAD, 0);
+#pragma unroll
+  for (int u = 0; u < RD - AHEAD; ++u) {
+    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+  }
+  __builtin_amdgcn_sched_group_barrier(0x008, MF - (RD - AHEAD), 0);
+}
+
 // C[sp] = (sum over the three piece pairs, k steps of split sp of A_p B_p^T) scaled back
 template <int TILE>
 __global__ __launch_bounds__(TILE * 2, 2) void pair_gemm_kernel(const _Float16* __restrict__ A,
@@ -119,7 +133,8 @@ __global__ __launch_bounds__(TILE * 2, 2) void pair_gemm_kernel(const _Float16* 
   const int64_t rowsA = (M - m0 < TILE) ? M - m0 : TILE;
   const int64_t rowsB = (N - n0 < TILE) ? N - n0 : TILE;
 
-  // lane -> (row of 8, 16-byte chunk): chunk c of row r sits at position c ^ (r & 7)
+  // lane -> (row of 8, 16-byte chunk): chunk c of row r sits at position c ^ ((r >> 1) & 7), so that the 16
+  // rows an LDS read serves at a time fall into different banks
   const int dr = lane >> 3, dc = (lane & 7) ^ (((wave & 1) << 2) | (dr >> 1));
   uint32_t voff[DPW];
 #pragma unroll
@@ -174,6 +189,7 @@ __global__ __launch_bounds__(TILE * 2, 2) void pair_gemm_kernel(const _Float16* 
             }
       }
     }
+    __builtin_amdgcn_sched_barrier(0);
     const unsigned char* Asm = gsm + st * STAGEB + (wr * (TILE / 2) + l32) * PLINE;
     const unsigned char* Bsm = gsm + st * STAGEB + TILEB + (wc * 64 + l32) * PLINE;
 #pragma unroll
@@ -209,6 +225,8 @@ __global__ __launch_bounds__(TILE * 2, 2) void pair_gemm_kernel(const _Float16* 
           a = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah[i], bl[j], a, 0, 0, 0);
         }
     }
+    spread_reads<4 * (TI + TJ), TI + TJ, 6 * TI * TJ>();
+    __builtin_amdgcn_sched_barrier(0);
     st ^= 1;
   }
 
