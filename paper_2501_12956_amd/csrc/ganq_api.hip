@@ -920,8 +920,10 @@ ganq_status ganq_quantize_layer(ganq_ctx* ctx, const void* W, ganq_dtype w_dtype
     const int cur = k & 1;
     {
       ProfScope prof(ctx, GANQ_K_T_PAD);
-      GANQ_HIP(ctx, launch_t_pad(s, Q, m, n, ldq, nbits, t_scratch, cur));
-      if (incremental && k > 0) GANQ_HIP(ctx, launch_t_flips(s, m, n, nbits, t_scratch, cur));
+      if (incremental && k > 0)
+        GANQ_HIP(ctx, launch_t_flips(s, Q, m, n, ldq, nbits, t_scratch, cur));
+      else
+        GANQ_HIP(ctx, launch_t_pad(s, Q, m, n, ldq, nbits, t_scratch, cur));
     }
     {
       ProfScope prof(ctx, GANQ_K_T_ACCUM, nullptr, k);

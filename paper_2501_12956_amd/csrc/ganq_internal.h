@@ -197,7 +197,7 @@ hipError_t launch_update_S(hipStream_t s, const float* W, int64_t m, int64_t n, 
 
 // T-update on one scratch region: integer digits of H (once per layer), padded copy of Q, the
 // one-hot GEMM with fold epilogue, and the per-row assembly + solve (G = W * H is an input,
-// computed once per layer).  From the second sweep of a layer on, launch_t_flips lists the columns
+// computed once per layer).  From the second sweep of a layer on, launch_t_flips makes the copy and lists the columns
 // whose code changed and launch_t_delta brings S_i H S_i^T up to date from them when they are few;
 // launch_t_accum and launch_t_delta are both enqueued and decide on the device which of them runs.
 hipError_t launch_t_prepare(hipStream_t s, const float* H, int64_t m, int64_t n, int64_t ldh,
@@ -206,7 +206,8 @@ hipError_t launch_t_prepare(hipStream_t s, const float* H, int64_t m, int64_t n,
 // previous sweep's)
 hipError_t launch_t_pad(hipStream_t s, const uint8_t* Q, int64_t m, int64_t n, int64_t ldq,
                         int nbits, void* scratch, int cur);
-hipError_t launch_t_flips(hipStream_t s, int64_t m, int64_t n, int nbits, void* scratch, int cur);
+hipError_t launch_t_flips(hipStream_t s, const uint8_t* Q, int64_t m, int64_t n, int64_t ldq, int nbits,
+                          void* scratch, int cur);
 hipError_t launch_t_accum(hipStream_t s, int64_t m, int64_t n, int nbits, void* scratch, int cur);
 hipError_t launch_t_delta(hipStream_t s, int64_t m, int64_t n, int nbits, void* scratch, int cur);
 // sweep: index of the alternation (0 for a stand-alone T-update); the choice made in it is logged

@@ -336,15 +336,10 @@ __device__ inline bool t_use_delta(const int* __restrict__ st, int64_t m, int64_
   return st[2] != 0 && st[3] != 0 && st[0] <= fmax && (int64_t)st[1] * kDeltaInv <= m * n;
 }
 
-// Zero-padded copy of Q (Qp, one byte per index).  One thread takes 16 consecutive indices (npad is a
-// multiple of 16); the codes come in one 16-byte load where the row of Q allows it.
-__global__ __launch_bounds__(256) void pad_q_kernel(const uint8_t* __restrict__ Q, int64_t m,
-                                                    int64_t n, int64_t ldq, int64_t npad, int nbits,
-                                                    int vec, uint8_t* __restrict__ Qp) {
-  const int64_t i = blockIdx.y;
-  const int64_t k0 = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 16;
-  if (k0 >= npad) return;
-  const int C = 1 << nbits;
+// Codes k0 .. k0 + 15 of row i, zero beyond the row and for rows that only fill a slab; one 16-byte load where
+// the row of Q allows it.
+__device__ inline uint4 padded_codes(const uint8_t* __restrict__ Q, int64_t i, int64_t m, int64_t n, int64_t ldq,
+                                     int64_t k0, int nbits, int vec) {
   uint32_t w[4] = {0u, 0u, 0u, 0u};
   if (i < m) {
     if (vec && k0 + 16 <= n) {
@@ -356,17 +351,28 @@ __global__ __launch_bounds__(256) void pad_q_kernel(const uint8_t* __restrict__ 
         if (k0 + t < n) w[t >> 2] |= (uint32_t)Q[i * ldq + k0 + t] << (8 * (t & 3));
     }
   }
-  const uint32_t cm = (uint32_t)(C - 1) * 0x01010101u;
-#pragma unroll
-  for (int u = 0; u < 4; ++u) w[u] &= cm;
-  *reinterpret_cast<uint4*>(Qp + i * npad + k0) = uint4{w[0], w[1], w[2], w[3]};
+  const uint32_t cm = ((1u << nbits) - 1u) * 0x01010101u;
+  return uint4{w[0] & cm, w[1] & cm, w[2] & cm, w[3] & cm};
+}
+
+// Zero-padded copy of Q (Qp, one byte per index); one thread takes 16 consecutive indices (npad is a
+// multiple of 16).
+__global__ __launch_bounds__(256) void pad_q_kernel(const uint8_t* __restrict__ Q, int64_t m,
+                                                    int64_t n, int64_t ldq, int64_t npad, int nbits,
+                                                    int vec, uint8_t* __restrict__ Qp) {
+  const int64_t i = blockIdx.y;
+  const int64_t k0 = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 16;
+  if (k0 >= npad) return;
+  *reinterpret_cast<uint4*>(Qp + i * npad + k0) = padded_codes(Q, i, m, n, ldq, k0, nbits, vec);
 }
 
 // ---- changed indices of a sweep ----
 // Row i: the columns whose code differs between the previous padded copy of Q and the current one,
 // in ascending order, as j | old << 16 | new << 20 (at most fmax are stored; Fcnt holds the true
-// count).
-__global__ __launch_bounds__(256) void t_flips_kernel(const uint8_t* __restrict__ Qn,
+// count).  The current copy is made here on the way: a launch less per sweep and a pass over it (256 x 512 4.8
+// of 9.5 us, 4096 x 4096 4 of 18).
+__global__ __launch_bounds__(256) void t_flips_kernel(const uint8_t* __restrict__ Q, int64_t m, int64_t n,
+                                                      int64_t ldq, int nbits, int vec, uint8_t* __restrict__ Qn,
                                                       const uint8_t* __restrict__ Qo, int64_t npad,
                                                       int fmax, uint32_t* __restrict__ Flist,
                                                       int* __restrict__ Fcnt) {
@@ -380,8 +386,9 @@ __global__ __launch_bounds__(256) void t_flips_kernel(const uint8_t* __restrict_
     const int64_t k = k0 + 16 * tid;
     uint4 qn = uint4{0u, 0u, 0u, 0u}, qo = uint4{0u, 0u, 0u, 0u};
     if (k < npad) {
-      qn = *reinterpret_cast<const uint4*>(Qn + i * npad + k);
       qo = *reinterpret_cast<const uint4*>(Qo + i * npad + k);
+      qn = padded_codes(Q, i, m, n, ldq, k, nbits, vec);
+      *reinterpret_cast<uint4*>(Qn + i * npad + k) = qn;
     }
     const uint32_t wn[4] = {qn.x, qn.y, qn.z, qn.w}, wo[4] = {qo.x, qo.y, qo.z, qo.w};
     int mine = 0;
@@ -1862,14 +1869,16 @@ hipError_t launch_t_pad(hipStream_t s, const uint8_t* Q, int64_t m, int64_t n, i
   return hipGetLastError();
 }
 
-// columns that changed between the padded copy of the previous sweep (buffer 1 - cur) and the
-// current one (buffer cur), per row, with their maximum and total
-hipError_t launch_t_flips(hipStream_t s, int64_t m, int64_t n, int nbits, void* scratch, int cur) {
+// the same, and the columns that changed between the padded copy of the previous sweep (buffer 1 - cur) and
+// this one, per row, with their maximum and total
+hipError_t launch_t_flips(hipStream_t s, const uint8_t* Q, int64_t m, int64_t n, int64_t ldq, int nbits,
+                          void* scratch, int cur) {
   TScratch sc;
   t_layout(m, n, nbits, (char*)scratch, &sc);
   const int64_t npad = t_npad(n), mpad = t_mpad(m, nbits);
-  hipLaunchKernelGGL(t_flips_kernel, dim3((unsigned)mpad), dim3(256), 0, s, sc.Qp[cur & 1], sc.Qp[(cur & 1) ^ 1],
-                     npad, sc.fmax, sc.Flist, sc.Fcnt);
+  const int vec = ((((uintptr_t)Q) & 15) == 0 && (ldq % 16) == 0) ? 1 : 0;
+  hipLaunchKernelGGL(t_flips_kernel, dim3((unsigned)mpad), dim3(256), 0, s, Q, m, n, ldq, nbits, vec,
+                     sc.Qp[cur & 1], sc.Qp[(cur & 1) ^ 1], npad, sc.fmax, sc.Flist, sc.Fcnt);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(t_chunks_kernel, dim3(1), dim3(1024), 0, s, sc.Fcnt, m, sc.fmax, sc.Cbase, sc.Tstat);
