@@ -8,7 +8,8 @@
 //     repeats the small shared part itself - it brings the 64 x 64 diagonal block up to date
 //     with the earlier inner blocks of the panel (left-looking, from L), factors it and
 //     inverts the factor in LDS - then updates its own rows the same way and multiplies
-//     them by that inverse.  No second launch and no grid-wide dependency for the solve.
+//     them by that inverse.  No second launch and no grid-wide dependency for the solve.  The
+//     serial chain of the four 16 x 16 leaves bounds it; the other wavefronts work beside it.
 //   outer panel: W22 -= L21 L21^T with K = 256, on the fp32 matrix cores or, for large remainders,
 //     as split products on the fp16 ones.
 #include "ganq_internal.h"

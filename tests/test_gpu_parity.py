@@ -167,6 +167,36 @@ def test_cholesky(ctx, n):
         assert np.linalg.norm(L2.cpu().numpy().astype(np.float64) - Lref) <= 1e-4 * np.linalg.norm(Lref)
 
 
+@pytest.mark.parametrize("n", [63, 128, 129, 191, 193, 256, 257, 321])
+def test_cholesky_rows_of_L_at_any_alignment(ctx, n):
+    """The panel kernel reads earlier columns of L in 16-byte words where its rows start on 16 bytes and one
+    by one elsewhere.  Edges of its 64 rows and columns; the factor has to hold for either.  Bound: a dot
+    product of n terms in fp32 errs by n 2^-24 of its absolute terms, and rows are multiplied by the inverse of a
+    64 x 64 block, which adds 64 2^-24 times the block's condition number."""
+    g = torch.Generator().manual_seed(n)
+    X = torch.randn(n, 4 * n, generator=g, dtype=torch.float64)
+    H32 = (X @ X.T).float()
+    H64 = H32.numpy().astype(np.float64)
+    Lref, _ = ref.cholesky(H64)
+    kappa = max(np.linalg.cond(Lref[i:i + 64, i:i + 64]) for i in range(0, n, 64))
+    bound = (n + 64 * kappa) * 2.0 ** -24 * np.linalg.norm(np.abs(Lref) @ np.abs(Lref).T)
+    ld = (n + 7) // 4 * 4
+    out = []
+    for stride, first in [(ld, 0), (ld + 1, 0), (ld, 1), (ld + 4, 4)]:
+        wide = torch.full((n, stride), 7.0, device="cuda")
+        view = wide[:, first:first + n]
+        L, info = ctx.cholesky(H32.cuda(), L=view)
+        assert info == 0
+        rest = torch.cat([wide[:, :first], wide[:, first + n:]], dim=1)
+        assert torch.equal(rest, torch.full_like(rest, 7.0))
+        L = L.cpu().numpy().astype(np.float64)
+        assert np.array_equal(L, np.tril(L)) and np.all(np.diag(L) > 0)
+        assert np.linalg.norm(L @ L.T - H64) <= bound
+        out.append(L)
+    if n <= 256:                                      # one outer panel: the same sums, read differently
+        assert all(np.array_equal(L, out[0]) for L in out[1:])
+
+
 def test_cholesky_preconditioning_modes(ctx):
     from paper_2501_12956_amd import binding as b
     rng = np.random.default_rng(3)
