@@ -128,6 +128,9 @@ __device__ __host__ inline int tile_digits(int flags) {
 }
 // exponent s_j of a row by the number of its tile's digits
 __device__ inline int tile_exponent(int P, int s2, int s3) { return P == 2 ? s2 : P == 3 ? s3 : s3 + 8; }
+// S3 of a row without off-diagonal entries: all its digits are 0 and any exponent will do, so its tile's
+// fold leaves it out (as a row of exponent 0 it would stretch the range that decides on the rounds)
+constexpr int kEmptyRow = -128;
 // 2^(f - 7 p) for the rows of round p of the fold, 0 for others
 __device__ inline uint8_t fold_factor(int f, int p) {
   f -= 7 * p;
@@ -200,7 +203,7 @@ __global__ __launch_bounds__(256) void t_rowscale_kernel(const float* __restrict
     if (yard > 0.f) need = 18 - ilogbf(yard);       // 2^-s <= 2^-18 yard, the bound that `two` tests
   }
   S2[j] = (int8_t)s2;
-  S3[j] = (int8_t)s3;
+  S3[j] = (int8_t)(mx == 0.f ? kEmptyRow : s3);
   Sneed[j] = (int16_t)need;
 }
 
@@ -220,7 +223,7 @@ __global__ __launch_bounds__(256) void t_split_kernel(const float* __restrict__ 
   const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;      // column
   if (k >= npad) return;
   const int P = tile_digits(Ptile[j / TM]);
-  const int sj = (j < n) ? tile_exponent(P, S2[j], S3[j]) : 0;
+  const int sj = (j < n && S3[j] != kEmptyRow) ? tile_exponent(P, S2[j], S3[j]) : 0;
   if (k == 0) Wj[j] = ldexpf(1.f, -sj);
   int iv = 0;
   if (j < n && k < n && k != j) {
@@ -305,7 +308,8 @@ __global__ __launch_bounds__(1024) void t_symscale_kernel(int* __restrict__ Ptil
   for (int t = tid >> 6; t < mtiles; t += 16) {
     const int P = tile_digits(Ptile[t]);
     const int64_t j0 = (int64_t)t * TM + lane, j1 = j0 + 64;
-    const int s0 = j0 < n ? tile_exponent(P, S2[j0], S3[j0]) : -1000, s1 = j1 < n ? tile_exponent(P, S2[j1], S3[j1]) : -1000;
+    const int s0 = j0 < n && S3[j0] != kEmptyRow ? tile_exponent(P, S2[j0], S3[j0]) : -1000;
+    const int s1 = j1 < n && S3[j1] != kEmptyRow ? tile_exponent(P, S2[j1], S3[j1]) : -1000;
     int hi = s0 > s1 ? s0 : s1, lo = hi;
     if (s0 > -1000) lo = min(lo, s0);
     if (s1 > -1000) lo = min(lo, s1);
@@ -315,6 +319,7 @@ __global__ __launch_bounds__(1024) void t_symscale_kernel(int* __restrict__ Ptil
       hi = max(hi, __shfl_xor(hi, o, 64));
       lo = min(lo, __shfl_xor(lo, o, 64));
     }
+    if (hi == -1000) hi = lo = 0;       // only empty rows
     F[j0] = fold_factor(hi - s0, 0);
     F[j1] = fold_factor(hi - s1, 0);
     if (lane == 0) {

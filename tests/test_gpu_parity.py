@@ -1100,6 +1100,27 @@ def test_update_T_both_digits_at_once(ctx, m, n, nbits, kind):
     assert err.max() <= 1e-4, err.max()
 
 
+@pytest.mark.parametrize("m,n,nbits,power", [(33, 2049, 4, -20), (40, 385, 4, -20), (40, 385, 3, 24), (70, 2303, 2, -20)])
+def test_update_T_rows_without_entries(ctx, m, n, nbits, power):
+    """Features that never occur, and one that meets no other, leave empty rows in H, whose digits are all 0
+    at any exponent: some in each tile, a whole tile, the last row (alone in its tile for some n), with H far
+    from unit scale.  The refit does not depend on a power of two in H, so the oracle's bound is that of the
+    other tests of these sums."""
+    H32 = _structured_H("weak", n, 33)
+    gone = [j for j in range(n) if j % 61 == 7 or 128 <= j < 256 or j == n - 1]
+    H32[gone, :] = 0
+    H32[:, gone] = 0
+    H32[200, 200] = H32[0, 0]                         # a feature that meets no other
+    H32 = np.ldexp(H32, power).astype(np.float32)
+    rng = np.random.default_rng(34)
+    W = (rng.standard_normal((m, n)) * 0.02).astype(np.float32)
+    Q = rng.integers(0, 1 << nbits, size=(m, n)).astype(np.uint8)
+    Tg = ctx.update_T(dev(W), dev(H32), dev(Q), dev(np.zeros((m, 1 << nbits), np.float32)), nbits).cpu().numpy()
+    Tref, _ = ref.update_T(W.astype(np.float64), H32.astype(np.float64), Q, nbits)
+    err = np.abs(Tg - Tref).max(axis=1) / np.abs(Tref).max(axis=1)
+    assert err.max() <= 1e-4, err.max()
+
+
 @pytest.mark.parametrize("n,events", [(130, (100,)), (1000, (990, 500)), (2200, (2150, 1500, 700))])
 def test_update_S_infinite_and_nan_weights(ctx, n, events):
     """An infinite weight makes an infinite residual whatever its code, and with it every target further
