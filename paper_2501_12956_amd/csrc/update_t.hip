@@ -1005,17 +1005,30 @@ __global__ __launch_bounds__(64 * TNW, 2) void t_accum_kernel(const int8_t* __re
       // that digit's weight and start again from 0.
       const int rounds = tile_rounds(tflags);
       const int sb1 = (st == 0) ? NS - 1 : st - 1, sb0 = (sb1 == 0) ? NS - 1 : sb1 - 1;
+      const int sbx = (sb0 == 0) ? NS - 1 : sb0 - 1;
+      if (rounds > 1) {
+        // row scales more than 2^6 apart: the factors of every round, over a stage that is no longer read
+        // (35 rounds of TM bytes at most, the operand of a stage has 8 KB).  Made anew for each round, between two
+        // barriers and with every strip folded, they took a refit of 2048 x 2048 with a feature 300 (10^4) times the
+        // others in each row tile from 250 to 290 (334) us; so it is 275 (268)
+        __syncthreads();
+        if (tid < TM) {
+          const int64_t row = jt0 + tid;
+          const int f = row < n_cols ? tile_smax(tflags) - tile_exponent(P, S2[row], S3[row]) : -1;
+          for (int p = 0; p < rounds; ++p) smem[sbx * STAGEB + p * TM + tid] = fold_factor(f, p);
+        }
+        __syncthreads();
+      }
 #pragma unroll 1
       for (int p = 0; p < rounds; ++p) {
+        constexpr int FOFF = T_ATILEB + (QS + 1) * 1024;       // foff = FOFF + kh * 4
+        const int fb0 = rounds > 1 ? sbx * STAGEB + p * TM - FOFF : sb0 * STAGEB;
+        const int fb1 = rounds > 1 ? sbx * STAGEB + p * TM + TK - FOFF : sb1 * STAGEB;
+        // rounds and strips of 32 rows without a row are left out (bit x: rows 4 x .. 4 x + 3)
+        uint32_t occupied = ~0u;
         if (p > 0) {
-          // row scales more than 2^6 apart: the factors of the next round take the place of the last one's
-          __syncthreads();
-          if (tid < TM) {
-            const int64_t row = jt0 + tid;
-            smem[(tid < TK ? sb0 : sb1) * STAGEB + T_ATILEB + (QS + 1) * 1024 + (tid & (TK - 1))] =
-                row < n_cols ? fold_factor(tile_smax(tflags) - tile_exponent(P, S2[row], S3[row]), p) : 0;
-          }
-          __syncthreads();
+          occupied = (uint32_t)__ballot(*reinterpret_cast<const uint32_t*>(smem + sbx * STAGEB + p * TM + l32 * 4) != 0);
+          if (occupied == 0) continue;
         }
         uint32_t bias = 0x00808080u;
         asm volatile("" : "+s"(bias));      // the digits are made anew in each round, not kept
@@ -1025,13 +1038,14 @@ __global__ __launch_bounds__(64 * TNW, 2) void t_accum_kernel(const int8_t* __re
           intx16 D[4];
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
+            if (i > 0 && (occupied >> (8 * i) & 0xffu) == 0) continue;
             const unsigned char* S0 = smem + (i < 2 ? sb0 : sb1) * STAGEB;
             int4v a, w[4];
 #pragma unroll
             for (int vq = 0; vq < 4; ++vq) {
               const int j = (i & 1) * 32 + vq * 8;      // of the stage, + kh * 4
               const uint32_t q = *reinterpret_cast<const uint32_t*>(S0 + qoff[jn] - kh * 16 + kh * 4 + j);
-              const uint32_t f = *reinterpret_cast<const uint32_t*>(S0 + foff + j);
+              const uint32_t f = *reinterpret_cast<const uint32_t*>(smem + (int)foff + ((i < 2 ? fb0 : fb1) + j));
               a[vq] = (int)maker.make(q, f);
               uint32_t z[4];
 #pragma unroll
