@@ -16,6 +16,8 @@
 // when they choose what to fetch and on the LDS side when they read MFMA fragments.  A 16-byte LDS
 // read serves 16 lanes at a time, so 16 consecutive rows must fall into different banks: a
 // permutation that repeated after 8 rows doubled the time of every fragment read (by the counters).
+#include <type_traits>
+
 #include "ganq_internal.h"
 
 namespace ganq {
@@ -35,6 +37,9 @@ constexpr int HNW = 8;          // wavefronts: 2 x 4, each 128 x 64 of the tile
 // All but the newest N of this wavefront's direct loads have arrived.
 template <int N>
 __device__ inline void wait_loads_but() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+
+// four floats on any 4-byte boundary: one 16-byte access all the same
+typedef floatx4 floatx4_dw __attribute__((aligned(4)));
 
 constexpr int TROWB = HT * 2;   // token-major stage: bytes per token row (256 features)
 
@@ -134,7 +139,8 @@ __global__ __launch_bounds__(64 * HNW) void hessian_f16_kernel(const _Float16* _
                                                               int64_t p, int64_t ldx, int64_t chunk,
                                                               int nt, int ntiles, int ngroups, int gsz,
                                                               int nsplit, float* __restrict__ partials,
-                                                              float* __restrict__ H, int64_t ldh, int accumulate) {
+                                                              float* __restrict__ H, int64_t ldh, int accumulate,
+                                                              int direct) {
   // Workgroups are dealt to the 8 XCDs round-robin by their flat index, so the 32 workgroups
   // with consecutive (blockIdx.x >> 3) run side by side on one XCD.  They take one group of at
   // most 32 tiles of one token split, and the groups are runs of the Z-order of the triangle:
@@ -289,8 +295,13 @@ __global__ __launch_bounds__(64 * HNW) void hessian_f16_kernel(const _Float16* _
   if constexpr (TOK) {
     if (nk > 0) {
 #pragma unroll
-      for (int u = 0; u < HS - 1; ++u) issue(u, u);
-      wait_loads_but<(HS - 2) * HLPS>();
+      for (int u = 0; u < HS - 1; ++u)
+        if (u < nk) issue(u, u);
+      // the count holds for a full set of requests
+      if (nk < HS - 1)
+        wait_all_loads();
+      else
+        wait_loads_but<(HS - 2) * HLPS>();
       __syncthreads();
       load_frags(f0, 0, 0);
     }
@@ -339,13 +350,15 @@ __global__ __launch_bounds__(64 * HNW) void hessian_f16_kernel(const _Float16* _
     }
   }
 
-  if (nsplit == 1) {
+  if (direct) {
     // The tile's sums are complete and go to both triangles of H from here: 8 calls of 2048 tokens at n =
     // 4096 took 66 + 26 us each with the second kernel, now 76.  What H held is requested three 32 x 32 tiles
-    // ahead (one tile at a time the loads alone take 25 us), and the mirrored elements are turned in a piece
-    // of LDS of the wavefront's own, so that they leave as whole lines (16-byte runs straight from the
-    // registers, or single elements in the tiles on the diagonal: 102 to 110 us).
-    const bool vec = (ldh % 4) == 0 && (((uintptr_t)H) & 15) == 0;
+    // ahead (one tile at a time the loads alone take 25 us), without branches, so that a wait can be for the oldest
+    // (64 tokens onto H, n = 2304: 23.6 us with branches, 21.3 without), and the mirrored elements are turned in a
+    // piece of LDS of the wavefront's own, so that they leave as whole lines (16-byte runs straight from the
+    // registers, or single elements in the tiles on the diagonal: 102 to 110 us), on whatever boundary the rows of H
+    // start: element by element where that is not 16 bytes, 2203 x 2048 took 70 us instead of 60, 8191 x 2048 241
+    // instead of 210.
     __syncthreads();          // nobody reads the stages any more
     constexpr int TLD = 36;   // floats per row of the piece
     float* piece = reinterpret_cast<float*>(hsm) + wave * (32 * TLD);
@@ -354,55 +367,69 @@ __global__ __launch_bounds__(64 * HNW) void hessian_f16_kernel(const _Float16* _
     float* __restrict__ up = H + (c0 + (lane >> 3)) * ldh + r0 + (lane & 7) * 4;
     // 32 x 32 tile t: nothing to do right of the diagonal; whole ones need no test per element
     auto empty = [&](int t) { return c0 + (t & 1) * 32 > r0 + (t >> 1) * 32 || r0 + (t >> 1) * 32 >= n; };
-    auto whole = [&](int t) { return vec && c0 + (t & 1) * 32 < r0 + (t >> 1) * 32 && r0 + (t >> 1) * 32 + 32 <= n; };
+    auto whole = [&](int t) { return c0 + (t & 1) * 32 < r0 + (t >> 1) * 32 && r0 + (t >> 1) * 32 + 32 <= n; };
     auto keep = [&](int t, int v) {
       const int64_t row = r0 + (t >> 1) * 32 + kh * 4 + (v >> 2) * 8 + (v & 3);
       return row < n && c0 + (t & 1) * 32 + l32 <= row;
     };
-    float old[8][16];
-    auto request = [&](int t) {
+    const int64_t rows = n - m0 < HT ? n - m0 : HT, cols = n - n0 < HT ? n - n0 : HT;
+    const __amdgpu_buffer_rsrc_t rsH = __builtin_amdgcn_make_buffer_rsrc(
+        H + m0 * ldh + n0, 0, (int)(((rows - 1) * ldh + cols) * 4), 0x00020000);      // below 2^31: checked by the host
+    const uint32_t lo = (uint32_t)(((wr * 128 + kh * 4) * ldh + wc * 64 + l32) * 4);
+    auto epilogue = [&](auto onto) {
+      constexpr bool ONTO = decltype(onto)::value;
+      float old[8][16];
+      auto request = [&](int t) {
 #pragma unroll
-      for (int v = 0; v < 16; ++v) old[t][v] = 0.f;
-      if (accumulate && !empty(t)) {
+        for (int v = 0; v < 16; ++v) {
+          const int row = (t >> 1) * 32 + (v >> 2) * 8 + (v & 3);
+          old[t][v] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+              rsH, whole(t) || keep(t, v) ? lo + (t & 1) * 128 : 0x80000000u, (int)(row * ldh * 4), 0));
+        }
+      };
+      if constexpr (ONTO) {
+        request(0);
+        request(1);
+        request(2);
+      }
 #pragma unroll
-        for (int v = 0; v < 16; ++v)
-          if (whole(t) || keep(t, v)) old[t][v] = low[((t >> 1) * 32 + (v >> 2) * 8 + (v & 3)) * ldh + (t & 1) * 32];
+      for (int t = 0; t < 8; ++t) {
+        if constexpr (ONTO) {
+          if (t + 3 < 8) request(t + 3);
+        }
+        if (empty(t)) continue;
+        floatx16& a = acc[t >> 1][t & 1];
+        const bool all = whole(t);
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          if constexpr (ONTO) a[v] += old[t][v];
+          if (all || keep(t, v)) low[((t >> 1) * 32 + (v >> 2) * 8 + (v & 3)) * ldh + (t & 1) * 32] = a[v];
+        }
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4)
+          *reinterpret_cast<floatx4*>(piece + l32 * TLD + q4 * 8 + kh * 4) =
+              floatx4{a[4 * q4], a[4 * q4 + 1], a[4 * q4 + 2], a[4 * q4 + 3]};
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          const floatx4 x = *reinterpret_cast<const floatx4*>(piece + (c * 8 + (lane >> 3)) * TLD + (lane & 7) * 4);
+          float* __restrict__ d = up + ((t & 1) * 32 + c * 8) * ldh + (t >> 1) * 32;
+          if (all) {
+            *reinterpret_cast<floatx4_dw*>(d) = x;
+          } else {
+            const int64_t col = c0 + (t & 1) * 32 + c * 8 + (lane >> 3), row = r0 + (t >> 1) * 32 + (lane & 7) * 4;
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+              if (row + u < n && col < row + u) d[u] = x[u];
+          }
+        }
+        __builtin_amdgcn_wave_barrier();
       }
     };
-    request(0);
-    request(1);
-    request(2);
-#pragma unroll
-    for (int t = 0; t < 8; ++t) {
-      if (t + 3 < 8) request(t + 3);
-      if (empty(t)) continue;
-      floatx16& a = acc[t >> 1][t & 1];
-      const bool all = whole(t);
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        a[v] += old[t][v];
-        if (all || keep(t, v)) low[((t >> 1) * 32 + (v >> 2) * 8 + (v & 3)) * ldh + (t & 1) * 32] = a[v];
-      }
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4)
-        *reinterpret_cast<floatx4*>(piece + l32 * TLD + q4 * 8 + kh * 4) =
-            floatx4{a[4 * q4], a[4 * q4 + 1], a[4 * q4 + 2], a[4 * q4 + 3]};
-      __builtin_amdgcn_wave_barrier();
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const floatx4 x = *reinterpret_cast<const floatx4*>(piece + (c * 8 + (lane >> 3)) * TLD + (lane & 7) * 4);
-        float* __restrict__ d = up + ((t & 1) * 32 + c * 8) * ldh + (t >> 1) * 32;
-        if (all) {
-          *reinterpret_cast<floatx4*>(d) = x;
-        } else {
-          const int64_t col = c0 + (t & 1) * 32 + c * 8 + (lane >> 3), row = r0 + (t >> 1) * 32 + (lane & 7) * 4;
-#pragma unroll
-          for (int u = 0; u < 4; ++u)
-            if (row + u < n && col < row + u) d[u] = x[u];
-        }
-      }
-      __builtin_amdgcn_wave_barrier();
-    }
+    if (accumulate)
+      epilogue(std::true_type{});
+    else
+      epilogue(std::false_type{});
     return;
   }
   float* out = partials + (int64_t)split * n * n;
@@ -493,6 +520,18 @@ int hessian_split(int64_t n, int64_t p) {
   return split;
 }
 
+// Whether a product's tiles go to H from its own epilogue; otherwise, and for split tokens, through a matrix of
+// partial sums and a second kernel.  What H held is waited for in the epilogue, by as many compute units as there are
+// tiles, while the second kernel is spread over all.  Here / second kernel, us, 64 tokens onto H: n = 32 11.3 / 8.7,
+// 256 17.8 / 13.6, 1024 20.3 / 17.1, 1536 (21 tiles) 20.6 / 18.9, 2047 (36) 25.9 / 25.5, 2048 21.1 / 23.6, 2304
+// 21.3 / 24.1, 4096 27.5 / 40.2; nothing held: 64 7.8 / 10.8, 96 9.7 / 11.4, 100 13.0 / 11.6, 127 13.2 / 12.0, 130
+// 11.9 / 12.1, 256 12.3 / 13.1, 1025 15.0 / 16.9, 2048 16.1 / 21.6.
+static bool hessian_direct(int64_t n, int split, int64_t ldh, int accumulate) {
+  const int64_t nt = ceil_div(n, HT);
+  if (split != 1 || ldh > ((int64_t)1 << 20)) return false;      // 32-bit offsets inside 256 rows of H
+  return accumulate ? nt * (nt + 1) / 2 >= 36 : n <= HT / 4 || n >= HT / 2;
+}
+
 size_t hessian_scratch_bytes(int64_t n, int64_t p) {
   if (p <= 0) return 0;
   return align_up((size_t)hessian_split(n, p) * (size_t)n * (size_t)n * sizeof(float));
@@ -517,7 +556,8 @@ hipError_t launch_hessian_f16(hipStream_t s, const _Float16* X, int64_t n, int64
                               float* H, int64_t ldh, int accumulate, float* partials) {
   if (ldx >= ((int64_t)1 << 22) || (p % 8) != 0 || (ldx % 8) != 0) return hipErrorInvalidValue;
   const int split = hessian_split(n, p);
-  int64_t chunk = ceil_div(ceil_div(p, split), HCHUNK) * HCHUNK;
+  const bool direct = hessian_direct(n, split, ldh, accumulate);
+  const int64_t chunk = ceil_div(ceil_div(p, split), HCHUNK) * HCHUNK;
   const int64_t nt = ceil_div(n, HT);
   const int ntiles = (int)(nt * (nt + 1) / 2);
   const int ngroups = (int)ceil_div(ntiles, 32), gsz = (int)ceil_div(ntiles, ngroups);
@@ -528,9 +568,9 @@ hipError_t launch_hessian_f16(hipStream_t s, const _Float16* X, int64_t n, int64
     if (ea != hipSuccess) return ea;
   }
   hipLaunchKernelGGL(hessian_f16_kernel<false>, grid, dim3(64 * HNW), hs(false) * hstageb(false), s, X, n, p, ldx, chunk,
-                     (int)nt, ntiles, ngroups, gsz, split, partials, H, ldh, accumulate);
+                     (int)nt, ntiles, ngroups, gsz, split, partials, H, ldh, accumulate, direct ? 1 : 0);
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess || split == 1) return e;
+  if (e != hipSuccess || direct) return e;
   dim3 g2((unsigned)ceil_div(n, 32), (unsigned)ceil_div(n, 32));
   hipLaunchKernelGGL(reduce_mirror_kernel, g2, dim3(256), 0, s, H, n, ldh, partials, n, split,
                      accumulate);
@@ -552,6 +592,7 @@ hipError_t launch_hessian_f16_tokens(hipStream_t s, const _Float16* Xt, int64_t 
                                      float* H, int64_t ldh, int accumulate, float* partials) {
   if (!hessian_tokens_direct_ok(Xt, n, p, ldxt)) return hipErrorInvalidValue;
   const int split = hessian_split(n, p);
+  const bool direct = hessian_direct(n, split, ldh, accumulate);
   const int64_t chunk = ceil_div(ceil_div(p, split), HCHUNK) * HCHUNK;
   const int64_t nt = ceil_div(n, HT);
   const int ntiles = (int)(nt * (nt + 1) / 2);
@@ -563,9 +604,9 @@ hipError_t launch_hessian_f16_tokens(hipStream_t s, const _Float16* Xt, int64_t 
     if (ea != hipSuccess) return ea;
   }
   hipLaunchKernelGGL(hessian_f16_kernel<true>, grid, dim3(64 * HNW), hs(true) * hstageb(true), s, Xt, n, p, ldxt, chunk,
-                     (int)nt, ntiles, ngroups, gsz, split, partials, H, ldh, accumulate);
+                     (int)nt, ntiles, ngroups, gsz, split, partials, H, ldh, accumulate, direct ? 1 : 0);
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess || split == 1) return e;
+  if (e != hipSuccess || direct) return e;
   dim3 g2((unsigned)ceil_div(n, 32), (unsigned)ceil_div(n, 32));
   hipLaunchKernelGGL(reduce_mirror_kernel, g2, dim3(256), 0, s, H, n, ldh, partials, n, split,
                      accumulate);

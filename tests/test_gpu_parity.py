@@ -1045,6 +1045,42 @@ def test_hessian_unsplit_product_writes_both_triangles(ctx, n, pad, tokens):
     assert bool((big[n:] == 7.0).all()) and bool((big[:, n:] == 7.0).all())
 
 
+@pytest.mark.parametrize("n,tokens", [(33, False), (64, True), (65, False), (127, False), (128, True), (161, False), (1791, False), (1792, True), (1793, False),
+                                      (2049, False), (2056, True), (2203, False), (2300, False)])
+@pytest.mark.parametrize("pad,shift", [(0, 0), (1, 0), (4, 0), (4, 1)])
+def test_hessian_unsplit_product_on_both_sides_of_its_rule(ctx, n, tokens, pad, shift):
+    """Added to H: 36 tiles and more by the product itself, fewer by a second kernel.  Nothing held: by the product
+    but for sizes between a quarter and half of a tile.  Rows of H on any boundary.  Small whole numbers: every sum
+    is exact."""
+    p = 40
+    g = torch.Generator(device="cuda").manual_seed(n + pad)
+    X = torch.randint(-3, 4, (n, p), generator=g, device="cuda")
+    want = (X.float() @ X.float().t()).double()
+    Xg = (X.t() if tokens else X).half().contiguous()
+    build = ctx.build_hessian_tokens if tokens else ctx.build_hessian
+    big = torch.full((n + 2, n + pad), 7.0, device="cuda")
+    H = big[1:n + 1, shift:n + shift]
+    build(Xg, H=H)
+    assert torch.equal(H.double(), want)
+    H.add_(torch.triu(torch.ones(n, n, device="cuda"), 1))           # what the upper triangle held is not read
+    build(Xg, H=H, accumulate=True)
+    assert torch.equal(H.double(), 2 * want)
+    assert bool((big[[0, n + 1]] == 7.0).all()) and bool((big[:, :shift] == 7.0).all()) and bool((big[:, n + shift:] == 7.0).all())
+
+
+@pytest.mark.parametrize("p", [1, 8, 32, 33, 64, 96, 100, 128, 129, 160, 161])
+def test_hessian_of_fewer_tokens_than_the_stages_hold(ctx, p):
+    """Token-major products of one step to just more than the five stages of 32 tokens."""
+    n = 264
+    g = torch.Generator(device="cuda").manual_seed(p)
+    X = torch.randint(-3, 4, (p, n), generator=g, device="cuda")
+    want = (X.float().t() @ X.float()).double()
+    H = ctx.build_hessian_tokens(X.half())
+    assert torch.equal(H.double(), want)
+    ctx.build_hessian_tokens(X.half(), H=H, accumulate=True)
+    assert torch.equal(H.double(), 2 * want)
+
+
 @pytest.mark.parametrize("n", [4353, 4480, 4607])
 def test_cholesky_trailing_updates_on_the_fp16_units(ctx, n):
     """The first trailing update of these sizes (more than 4096 rows below the panel; whole tiles, ragged
