@@ -715,21 +715,26 @@ __device__ inline void split_digits(const uint32_t (&z)[4], int4v (&w)[4], int v
 }
 
 // D[d][v] = element (row (v>>2)*8 + kh*4 + (v&3), column l32) of digit d's fold: rows are (i', a), columns
-// (i'', b) of a column tile; i' == i'' is kept.  dst: this lane's column of M_i.
+// (i'', b) of a column tile; i' == i'' is kept, which are fold_rows of a lane's registers.
+constexpr int fold_rows(int nbits) { return nbits == 4 ? 8 : 4; }
 template <int NBITS>
-__device__ inline void store_fold(const intx16 (&D)[4], float* __restrict__ dst, int l32, int kh, float weight, bool add) {
-  constexpr int C = 1 << NBITS;
-  float old[16];
+__device__ inline int fold_row(int x, int l32, int kh) {
+  const int v = (l32 >> (NBITS == 4 ? 4 : 3)) * fold_rows(NBITS) + x;      // register
+  return (v >> 2) * 8 + kh * 4 + (v & 3);
+}
+// S[x] += weight * the sum that D's digits make at row x of these
+template <int NBITS>
+__device__ inline void add_fold(const intx16 (&D)[4], float (&S)[fold_rows(NBITS)], int l32, float weight) {
+  constexpr int SR = fold_rows(NBITS);
 #pragma unroll
-  for (int v = 0; v < 16; ++v) {
-    const int row = (v >> 2) * 8 + kh * 4 + (v & 3);
-    old[v] = (add && (row >> NBITS) == (l32 >> NBITS)) ? dst[(row & (C - 1)) * C] : 0.f;
-  }
+  for (int x = 0; x < SR; ++x) {
+    float z = 0.f;
 #pragma unroll
-  for (int v = 0; v < 16; ++v) {
-    const int row = (v >> 2) * 8 + kh * 4 + (v & 3);
-    const float z = fmaf((float)(D[3][v] * 256 + D[2][v]), 65536.f, (float)(D[1][v] * 256 + D[0][v]));
-    if ((row >> NBITS) == (l32 >> NBITS)) dst[(row & (C - 1)) * C] = fmaf(z, weight, old[v]);
+    for (int v = x; v < 16; v += SR) {
+      const float zv = fmaf((float)(D[3][v] * 256 + D[2][v]), 65536.f, (float)(D[1][v] * 256 + D[0][v]));
+      z = (v / SR == l32 >> (NBITS == 4 ? 4 : 3)) ? zv : z;
+    }
+    S[x] = fmaf(z, weight, S[x]);
   }
 }
 
@@ -794,10 +799,12 @@ __global__ __launch_bounds__(64 * TNW, 2) void t_accum_kernel(const int8_t* __re
   const uint32_t coff = (uint32_t)(T_ATILEB + QS * 1024 + kh * 16), foff = (uint32_t)(T_ATILEB + (QS + 1) * 1024 + kh * 4);
   const OneHotMaker<NBITS> maker(lane & (C - 1));
   // code loads: slot u < QS holds rows 16 u .. 16 u + 15 of the slab, slot QS the one-hot values of the
-  // columns, slot QS + 1 the fold's factors of the rows of the same numbers (64 bytes each; the other
-  // lanes' offsets lie beyond any descriptor and move nothing); further slots only even out the count
+  // columns, slot QS + 1 the fold's factors of the rows of the same numbers and behind them the exponents of these
+  // rows (64 bytes each; the other lanes' offsets lie beyond any descriptor and move nothing); further slots only
+  // even out the count
   constexpr uint32_t NOWHERE = 0x80000000u;
-  const int4v rsQ = make_rsrc(Qp + i0 * npad, (int64_t)RW * npad), rsC = make_rsrc(Cs, npad), rsF = make_rsrc(Fj, npad);
+  const int4v rsQ = make_rsrc(Qp + i0 * npad, (int64_t)RW * npad), rsC = make_rsrc(Cs, npad);
+  const int4v rsF = make_rsrc(S2, (int64_t)((const uint8_t*)Fj - (const uint8_t*)S2) + npad);      // S2, S3, factors
   const uint32_t vq = (uint32_t)((lane >> 2) * npad + (lane & 3) * 16), vc = lane < TK / 16 ? (uint32_t)(lane * 16) : NOWHERE;
 
   // direct load of the A tile: one instruction covers 16 rows x 64 bytes; TM / 16 of them are
@@ -825,6 +832,9 @@ __global__ __launch_bounds__(64 * TNW, 2) void t_accum_kernel(const int8_t* __re
     const int tflags = __builtin_amdgcn_readfirstlane(Ptile[mt]);
     const int P = tile_digits(tflags);
     const bool shared_acc = ds == 1 && tile_shared_acc(tflags);   // the digits may share the accumulators
+    const uint32_t vf = lane < TK / 16       ? (uint32_t)(Fj - (const uint8_t*)S2) + (uint32_t)(lane * 16)
+                        : lane < 2 * TK / 16 ? (P == 2 ? 0u : (uint32_t)(S3 - S2)) + (uint32_t)(lane * 16 - TK)
+                                             : NOWHERE;
 
     struct Codes {
       int4v q[2], c;            // codes of the two column tiles and one-hot values of a half step
@@ -888,7 +898,7 @@ __global__ __launch_bounds__(64 * TNW, 2) void t_accum_kernel(const int8_t* __re
       for (int u = 0; u < LPS; ++u) {
         const int slot = wave + TNW * (u - ALD);
         pv[u] = u < ALD ? voff[u < ALD ? u : 0]
-                        : slot < QS ? vq + (uint32_t)(16 * slot * npad) : slot < QS + 2 ? vc : NOWHERE;
+                        : slot < QS ? vq + (uint32_t)(16 * slot * npad) : slot == QS ? vc : slot == QS + 1 ? vf : NOWHERE;
       }
       auto issue_source = [&]() {
         if (pk == nk - TM / TK) {
@@ -1006,39 +1016,58 @@ __global__ __launch_bounds__(64 * TNW, 2) void t_accum_kernel(const int8_t* __re
       const int rounds = tile_rounds(tflags);
       const int sb1 = (st == 0) ? NS - 1 : st - 1, sb0 = (sb1 == 0) ? NS - 1 : sb1 - 1;
       const int sbx = (sb0 == 0) ? NS - 1 : sb0 - 1;
+      constexpr int FOFF = T_ATILEB + (QS + 1) * 1024;       // foff = FOFF + kh * 4
       if (rounds > 1) {
         // row scales more than 2^6 apart: the factors of every round, over a stage that is no longer read
-        // (35 rounds of TM bytes at most, the operand of a stage has 8 KB).  Made anew for each round, between two
-        // barriers and with every strip folded, they took a refit of 2048 x 2048 with a feature 300 (10^4) times the
-        // others in each row tile from 250 to 290 (334) us; so it is 275 (268)
+        // (35 rounds of TM bytes at most, the operand of a stage has 8 KB)
         __syncthreads();
         if (tid < TM) {
-          const int64_t row = jt0 + tid;
-          const int f = row < n_cols ? tile_smax(tflags) - tile_exponent(P, S2[row], S3[row]) : -1;
+          const int sj = (int8_t)smem[(tid < TK ? sb0 : sb1) * STAGEB + FOFF + TK + (tid & (TK - 1))];
+          const int f = jt0 + tid < n_cols ? tile_smax(tflags) - (P == 4 ? sj + 8 : sj) : -1;
           for (int p = 0; p < rounds; ++p) smem[sbx * STAGEB + p * TM + tid] = fold_factor(f, p);
         }
         __syncthreads();
       }
-#pragma unroll 1
-      for (int p = 0; p < rounds; ++p) {
-        constexpr int FOFF = T_ATILEB + (QS + 1) * 1024;       // foff = FOFF + kh * 4
-        const int fb0 = rounds > 1 ? sbx * STAGEB + p * TM - FOFF : sb0 * STAGEB;
-        const int fb1 = rounds > 1 ? sbx * STAGEB + p * TM + TK - FOFF : sb1 * STAGEB;
-        // rounds and strips of 32 rows without a row are left out (bit x: rows 4 x .. 4 x + 3)
-        uint32_t occupied = ~0u;
-        if (p > 0) {
-          occupied = (uint32_t)__ballot(*reinterpret_cast<const uint32_t*>(smem + sbx * STAGEB + p * TM + l32 * 4) != 0);
-          if (occupied == 0) continue;
-        }
-        uint32_t bias = 0x00808080u;
-        asm volatile("" : "+s"(bias));      // the digits are made anew in each round, not kept
-        const float weight = ldexpf(1.f, 7 * p - tile_smax(tflags) + (shared_acc ? 0 : 8 * (P - 1 - dg)));
 #pragma unroll
-        for (int jn = 0; jn < 2; ++jn) {
+      for (int jn = 0; jn < 2; ++jn) {
+        // On top of what this same thread stored before, requested ahead of the first round; the rounds add up in
+        // registers.  With a store and a load per round, the exponents from memory and the first strip folded in every
+        // round, refits with a feature 300 (10^4) times the others in each row tile took 163 (270) us instead of 155
+        // (241) at 2048 x 2048, 73 (115) instead of 69 (103) at 256 x 2048; with the scales of all features spread
+        // over 2^10 283 instead of 258, 119 instead of 107.  Digits made once for two rounds (16 x 16 sums of 4
+        // registers instead of 16) spilled: 278.
+        const int col = wave * 64 + jn * 32 + l32, il = col >> NBITS;
+        float* __restrict__ dst = Apart + ((int64_t)part * mpad + i0 + il) * C * C + (col & (C - 1));
+        constexpr int SR = fold_rows(NBITS);
+        float S[SR];
+#pragma unroll
+        for (int x = 0; x < SR; ++x) {
+          const int rr = fold_row<NBITS>(x, l32, kh);
+          S[x] = (stored && (rr >> NBITS) == (l32 >> NBITS)) ? dst[(rr & (C - 1)) * C] : 0.f;
+        }
+#pragma unroll 1
+        for (int p = 0; p < rounds; ++p) {
+          const int fb0 = rounds > 1 ? sbx * STAGEB + p * TM - FOFF : sb0 * STAGEB;
+          const int fb1 = rounds > 1 ? sbx * STAGEB + p * TM + TK - FOFF : sb1 * STAGEB;
+          // rounds and strips of 32 rows without a row are left out (bit x: rows 4 x .. 4 x + 3)
+          uint32_t occupied = ~0u;
+          if (p > 0) {
+            occupied = (uint32_t)__ballot(*reinterpret_cast<const uint32_t*>(smem + sbx * STAGEB + p * TM + l32 * 4) != 0);
+            if (occupied == 0) continue;
+          }
+          uint32_t bias = 0x00808080u;
+          asm volatile("" : "+s"(bias));      // the digits are made anew in each round, not kept
+          const float weight = ldexpf(1.f, 7 * p - tile_smax(tflags) + (shared_acc ? 0 : 8 * (P - 1 - dg)));
           intx16 D[4];
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            if (i > 0 && (occupied >> (8 * i) & 0xffu) == 0) continue;
+            if ((occupied >> (8 * i) & 0xffu) == 0) {
+              if (i == 0) {
+#pragma unroll
+                for (int d = 0; d < 4; ++d) D[d] = intx16{};
+              }
+              continue;
+            }
             const unsigned char* S0 = smem + (i < 2 ? sb0 : sb1) * STAGEB;
             int4v a, w[4];
 #pragma unroll
@@ -1057,10 +1086,12 @@ __global__ __launch_bounds__(64 * TNW, 2) void t_accum_kernel(const int8_t* __re
               D[d] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, w[d], i == 0 ? intx16{} : D[d], 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
           }
-          // later folds add to what this same thread stored after the first
-          const int col = wave * 64 + jn * 32 + l32, il = col >> NBITS;
-          store_fold<NBITS>(D, Apart + ((int64_t)part * mpad + i0 + il) * C * C + (col & (C - 1)), l32, kh, weight,
-                            stored || p > 0);
+          add_fold<NBITS>(D, S, l32, weight);
+        }
+#pragma unroll
+        for (int x = 0; x < SR; ++x) {
+          const int rr = fold_row<NBITS>(x, l32, kh);
+          if ((rr >> NBITS) == (l32 >> NBITS)) dst[(rr & (C - 1)) * C] = S[x];
         }
       }
       stored = true;
@@ -1345,7 +1376,7 @@ __global__ __launch_bounds__(64 * TNW, 1) void t_accum2_kernel(const int8_t* __r
   };
 
   // sums of an item: the registers whose rows can be this lane's i'
-  constexpr int SR = NBITS == 4 ? 8 : 4;
+  constexpr int SR = fold_rows(NBITS);
   float S[2][SR];
 #pragma unroll
   for (int jn = 0; jn < 2; ++jn)
@@ -1396,17 +1427,7 @@ __global__ __launch_bounds__(64 * TNW, 1) void t_accum2_kernel(const int8_t* __r
         if (i < 2) prepare(i + 2);
         __builtin_amdgcn_sched_barrier(0);
       }
-      // of the 16 registers those whose rows are this lane's i': row (v>>2)*8 + kh*4 + (v&3), i' = row >> NBITS
-#pragma unroll
-      for (int x = 0; x < SR; ++x) {
-        float z = 0.f;
-#pragma unroll
-        for (int v = x; v < 16; v += SR) {
-          const float zv = fmaf((float)(D[3][v] * 256 + D[2][v]), 65536.f, (float)(D[1][v] * 256 + D[0][v]));
-          z = (v / SR == l32 >> (NBITS == 4 ? 4 : 3)) ? zv : z;
-        }
-        S[jn][x] = fmaf(z, weight, S[jn][x]);
-      }
+      add_fold<NBITS>(D, S[jn], l32, weight);
     }
     const Tile was = ct;
     const bool more = next_tile(ct);
@@ -1417,8 +1438,7 @@ __global__ __launch_bounds__(64 * TNW, 1) void t_accum2_kernel(const int8_t* __r
       float* __restrict__ dst = Apart + ((int64_t)(was.group * mpad + was.i0) + il) * C * C + (col & (C - 1));
 #pragma unroll
       for (int x = 0; x < SR; ++x) {
-        const int row = (l32 >> (NBITS == 4 ? 4 : 3)) * SR + x;      // register
-        const int rr = (row >> 2) * 8 + kh * 4 + (row & 3);
+        const int rr = fold_row<NBITS>(x, l32, kh);
         if ((rr >> NBITS) == (l32 >> NBITS)) dst[(rr & (C - 1)) * C] = S[jn][x];
         S[jn][x] = 0.f;
       }

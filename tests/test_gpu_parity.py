@@ -1157,6 +1157,31 @@ def test_update_T_rows_without_entries(ctx, m, n, nbits, power):
     assert err.max() <= 1e-4, err.max()
 
 
+@pytest.mark.parametrize("nbits", [1, 2, 3, 4])
+@pytest.mark.parametrize("m,n,large", [(40, 385, {5: 300.0, 383: 1e4}), (33, 300, {j: 300.0 for j in range(0, 300, 24)}),
+                                       (150, 640, {130: 1e4, 250: 300.0, 639: 40.0}), (17, 130, {129: 300.0}),
+                                       (1100, 1030, {j: 500.0 for j in range(96, 1030, 128)})])
+def test_update_T_row_scales_in_several_rounds(ctx, nbits, m, n, large):
+    """Features far above the others of their row tile: the sums of the tile are folded in two to three rounds, with
+    rows in the first strip of 32 or not, in one strip or in all, in the last rows of a tile that is not full, digits
+    in workgroups of their own (small m) or not.  The bound is that of the other tests of these sums, 1e-4: a feature
+    s times the others enters the fp32 sums G = W H of every column through its correlations, about 2 / sqrt(4096)
+    of s, so T is known to some 2^-24 s / 32 times the loss of cancellation: 2e-5 at s = 10^4, more where few
+    columns share a code (n = 130 over 16 codes: s = 300)."""
+    H32 = _structured_H("weak", n, n)
+    d = np.ones(n)
+    d[list(large)] = list(large.values())
+    H32 = (H32 * d[:, None] * d[None, :]).astype(np.float32)
+    rng = np.random.default_rng(35)
+    W = (rng.standard_normal((m, n)) * 0.02).astype(np.float32)
+    Q = rng.integers(0, 1 << nbits, size=(m, n)).astype(np.uint8)
+    Tg = ctx.update_T(dev(W), dev(H32), dev(Q), dev(np.zeros((m, 1 << nbits), np.float32)), nbits).cpu().numpy()
+    rows = np.unique(np.linspace(0, m - 1, 40).astype(int))
+    Tref, _ = ref.update_T(W[rows].astype(np.float64), H32.astype(np.float64), Q[rows], nbits)
+    err = np.abs(Tg[rows] - Tref).max(axis=1) / np.abs(Tref).max(axis=1)
+    assert err.max() <= 1e-4, err.max()
+
+
 @pytest.mark.parametrize("n,events", [(130, (100,)), (1000, (990, 500)), (2200, (2150, 1500, 700))])
 def test_update_S_infinite_and_nan_weights(ctx, n, events):
     """An infinite weight makes an infinite residual whatever its code, and with it every target further
