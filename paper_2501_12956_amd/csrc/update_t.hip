@@ -223,7 +223,8 @@ __global__ __launch_bounds__(256) void t_split_kernel(const float* __restrict__ 
   const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;      // column
   if (k >= npad) return;
   const int P = tile_digits(Ptile[j / TM]);
-  const int sj = (j < n && S3[j] != kEmptyRow) ? tile_exponent(P, S2[j], S3[j]) : 0;
+  // (a row without entries has all digits 0 at any exponent)
+  const int sj = (j < n) ? ((P == 2) ? S2[j] : (P == 3) ? S3[j] : S3[j] + 8) : 0;
   if (k == 0) Wj[j] = ldexpf(1.f, -sj);
   int iv = 0;
   if (j < n && k < n && k != j) {
