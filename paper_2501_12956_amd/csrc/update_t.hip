@@ -45,6 +45,7 @@
 // update pays off below about 3.5 % changed indices (t_delta_kernel; the choice is made on the
 // device, per sweep, from the counts of the kernel that lists the changes).  The state A_i is kept
 // in float64 and every change is an exact integer sum scaled by a power of two.
+#include <algorithm>
 #include <type_traits>
 
 #include "ganq_internal.h"
@@ -1450,7 +1451,7 @@ __global__ __launch_bounds__(64 * TNW, 1) void t_accum2_kernel(const int8_t* __r
 }
 
 // ---- per-row assembly and solve (one wavefront per row, float64) ----
-__global__ __launch_bounds__(64) void t_solve_kernel(const float* __restrict__ Apart, int ngroups,
+__global__ __launch_bounds__(64) void t_solve_kernel(const float* __restrict__ Apart, int nparts, int nboth,
                                                      const int* __restrict__ Tstat, int fmax, int64_t m_rows,
                                                      double* __restrict__ Astate, int* __restrict__ Tlog,
                                                      const int* __restrict__ Cbase,
@@ -1584,6 +1585,8 @@ __global__ __launch_bounds__(64) void t_solve_kernel(const float* __restrict__ A
     const int64_t gs = mpad * C * C;
     // all loads of up to 16 groups x 4 entries are issued before the first is used: one round
     // trip to memory instead of one per four groups
+    // partial sums of t_accum_kernel, or of t_accum2_kernel where that one may run and did
+    const int ngroups = (nboth > 0 && Tstat[5] != 0) ? nboth : nparts;
     const float* __restrict__ P0 = Apart + i * C * C + tid;
     double sacc[4] = {0.0, 0.0, 0.0, 0.0};
     for (int g0 = 0; g0 < ngroups; g0 += 16) {
@@ -1755,17 +1758,21 @@ inline int64_t t_npad(int64_t n) { return ceil_div(n, TM) * TM; }
 inline int64_t t_mpad(int64_t m, int nbits) { const int64_t rw = TN >> nbits; return ceil_div(m, rw) * rw; }
 inline int t_groups(int64_t n) { return (int)((ceil_div(n, TM) + 1) / 2); }
 
-// Whether a sweep may go to t_accum2_kernel (if all tiles suit it, which the device knows).  Its second launch
-// costs a sweep 5 us.  Pass per digit / both at once, us: many items 2048 x 2048 140 / 143, 4096 x 4096 902 /
-// 900 (3 bits 441 / 455, 2 bits 229 / 233), 4096 x 6144 1921 / 1880, 4096 x 11008 at 3 bits 2825 / 2774, 1024 x 16384
-// 3134 / 2870; no more items than compute units, where a lone workgroup has the unit to itself: 512 x 2048
-// 51 / 41, 256 x 4096 82 / 62, 512 x 1024 at 3 bits 32 / 27.
+// Whether a sweep may go to t_accum2_kernel (if all tiles suit it, which the device knows; a launch that returns
+// costs 2 to 5 us).  Pass per digit / both at once, us, where they suit it.  Many items: 4096 x 6144 1791 / 1746 (3
+// bits 907 / 913, 2 bits 508 / 498, 1 bit 353 / 300), 2048 x 11008 2850 / 2612 (1373 / 1327, 787 / 773, 541 / 433),
+// 512 x 28672 4697 / 4207 (2368 / 2080, 1312 / 1276, 864 / 725); shorter ones 2048 x 2048 140 / 143, 4096 x 4096 902 /
+// 900 (441 / 455, 229 / 233).  No more items than compute units, where a workgroup has a unit to itself, against a workgroup per digit:
+// 4 bits 512 x 2048 61.0 / 60.4, 368 x 2816 73.2 / 69.1, 256 x 4096 88 / 82, 128 x 8192 147 / 131; 1 bit 4096 x 2048
+// 75.8 / 77.5, 2048 x 4096 93 / 86.  (Of a quarter as many items the digits alone would be faster: 64 x 4096 67.5 / 75.5.)
 inline bool t_two_digits(int64_t n, int64_t items) { return n >= 6144 || (items <= 256 && n >= 2048); }
 
-// Workgroups per item: as many, up to one per digit, as the chip takes at once (two per compute unit) and the
-// scratch holds partial sums for.  256 x 512 (32 items, three digits) 41 -> 17 us.
-inline int t_digit_split(int64_t n, int64_t items, int64_t room) {
-  int ds = t_two_digits(n, items) ? 1 : TP;
+// Workgroups per item of t_accum_kernel: as many, up to one per digit, as the chip takes at once (two per compute
+// unit) and the scratch holds partial sums for.  256 x 512 (32 items, three digits) 41 -> 17 us.  Also where
+// t_accum2_kernel may run, for matrices that do not suit it: 128 x 2048 with three digits 92 -> 71 us, with a feature
+// 300 times the others in each row tile 69 -> 52, 256 x 4096 138 -> 112.
+inline int t_digit_split(int64_t items, int64_t room) {
+  int ds = TP;
   while (ds > 1 && (items * ds > 512 || ds > room)) --ds;
   return ds;
 }
@@ -1837,7 +1844,7 @@ inline size_t t_layout(int64_t m, int64_t n, int nbits, char* base, TScratch* ou
   const size_t o_fl = take((size_t)mpad * fmax * sizeof(uint32_t));
   const size_t o_dp = take((size_t)max_chunks * C * C * sizeof(double));
   if (out != nullptr) {
-    out->ds = t_digit_split(n, mpad / (TN >> nbits) * t_groups(n), (int64_t)((off - o_ap) / part) / t_groups(n));
+    out->ds = t_digit_split(mpad / (TN >> nbits) * t_groups(n), (int64_t)((off - o_ap) / part) / t_groups(n));
     out->scale = (float*)(base + o_scale);
     out->Hdiag = (float*)(base + o_diag);
     out->Cs = (uint8_t*)(base + o_cs);
@@ -1941,7 +1948,7 @@ static hipError_t launch_t_accum_n(hipStream_t s, int64_t m, int64_t n, void* sc
     // this one or the next returns at once (Tstat[5]); one workgroup per compute unit walks its items
     const int shmem = d_stages(NBITS) * d_stage_bytes(NBITS);
     if ((e = ensure_dynamic_lds((const void*)t_accum2_kernel<NBITS>, shmem, lds_set2)) != hipSuccess) return e;
-    hipLaunchKernelGGL(t_accum2_kernel<NBITS>, dim3((unsigned)(wgs < 256 ? wgs : 256)), dim3(64 * TNW),
+    hipLaunchKernelGGL(t_accum2_kernel<NBITS>, dim3((unsigned)std::min<int64_t>(8 * ceil_div(items, 8), 256)), dim3(64 * TNW),
                        shmem, s, sc.Hs, sc.Hd, sc.Tstat, sc.fmax, m, n, npad, sc.Qp[cur & 1], sc.Cs,
                        (const uint8_t*)sc.Sneed, mpad, mtiles, groups, sc.Apart);
     if ((e = hipGetLastError()) != hipSuccess) return e;
@@ -1992,7 +1999,9 @@ hipError_t launch_t_solve(hipStream_t s, const float* G, int64_t ldg, int64_t m,
   t_layout(m, n, nbits, (char*)scratch, &sc);
   const int64_t mpad = t_mpad(m, nbits);
   int* tlog = (sweep >= 0 && sweep < kTLogMax) ? sc.Tstat + 8 + 3 * sweep : nullptr;
-  hipLaunchKernelGGL(t_solve_kernel, dim3((unsigned)m), dim3(64), 0, s, sc.Apart, t_groups(n) * sc.ds, sc.Tstat, sc.fmax,
+  const int groups = t_groups(n);
+  const int nboth = t_two_digits(n, mpad / (TN >> nbits) * groups) ? groups : 0;
+  hipLaunchKernelGGL(t_solve_kernel, dim3((unsigned)m), dim3(64), 0, s, sc.Apart, groups * sc.ds, nboth, sc.Tstat, sc.fmax,
                      m, sc.Astate, tlog, sc.Cbase, sc.Dpart, sc.Vstate, sc.Nstate, sc.Flist, sc.Fcnt, mpad, sc.scale,
                      sc.Hdiag, G, ldg, Q, ldq, n, nbits,
                      empty_mode, T, empty_count);

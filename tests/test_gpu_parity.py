@@ -1182,6 +1182,43 @@ def test_update_T_row_scales_in_several_rounds(ctx, nbits, m, n, large):
     assert err.max() <= 1e-4, err.max()
 
 
+@pytest.mark.parametrize("m,n,nbits,kind", [(20, 2100, 4, "medium"), (33, 2304, 3, "strong"), (130, 2049, 2, "wide"),
+                                            (200, 2176, 1, "mixed"), (16, 6150, 4, "medium")])
+def test_update_T_few_rows_split_by_digit(ctx, m, n, nbits, kind):
+    """Few rows of a wide layer whose H does not suit the kernel that takes both digits at once: each digit has
+    workgroups and partial sums of its own, which the solve adds up."""
+    H32 = _structured_H(kind, n, 36)
+    rng = np.random.default_rng(37)
+    W = (rng.standard_normal((m, n)) * 0.02).astype(np.float32)
+    Q = rng.integers(0, 1 << nbits, size=(m, n)).astype(np.uint8)
+    Tg = ctx.update_T(dev(W), dev(H32), dev(Q), dev(np.zeros((m, 1 << nbits), np.float32)), nbits).cpu().numpy()
+    rows = np.unique(np.linspace(0, m - 1, 24).astype(int))
+    Tref, _ = ref.update_T(W[rows].astype(np.float64), H32.astype(np.float64), Q[rows], nbits)
+    err = np.abs(Tg[rows] - Tref).max(axis=1) / np.abs(Tref).max(axis=1)
+    assert err.max() <= 1e-4, err.max()
+
+
+def test_quantize_layer_few_rows_split_by_digit_and_updating(ctx):
+    """The partial sums of the digits lie over the areas of the sweeps that update from the changed columns; a layer
+    with both kinds of sweeps (two digits, features of one scale, whose sums are too large for the digits to share an
+    integer) ends in the least-squares refit to its indices and repeats itself."""
+    m, n, nbits, K = 40, 3712, 4, 60
+    W, _ = make_problem(m, n, 8, nbits)
+    X = torch.randn(n, 16 * n, generator=torch.Generator(device="cuda").manual_seed(38), device="cuda", dtype=torch.float16)
+    H = ctx.build_hessian(X)
+    L, info = ctx.cholesky(H)
+    assert info == 0
+    T, Q = ctx.quantize_layer(W.cuda(), H, nbits, K, L=L)
+    log = ctx.sweep_log()
+    T2, Q2 = ctx.quantize_layer(W.cuda(), H, nbits, K, L=L)
+    assert torch.equal(T, T2) and torch.equal(Q, Q2)
+    updated = [bool(u) for u, _, _ in log]
+    assert any(updated) and not all(updated[1:]), log[-3:]
+    Tref, _ = ref.update_T(W.numpy().astype(np.float64), H.cpu().numpy().astype(np.float64), Q.cpu().numpy(), nbits)
+    err = np.abs(T.cpu().numpy() - Tref).max(axis=1) / np.abs(Tref).max(axis=1)
+    assert err.max() <= 1e-4, err.max()
+
+
 @pytest.mark.parametrize("n,events", [(130, (100,)), (1000, (990, 500)), (2200, (2150, 1500, 700))])
 def test_update_S_infinite_and_nan_weights(ctx, n, events):
     """An infinite weight makes an infinite residual whatever its code, and with it every target further
