@@ -295,14 +295,16 @@ __device__ inline void leaf_update(float (*M)[BLD], int i, int j, int k) {
   leaf_store(M, 16 * i, 16 * j, d);
 }
 // Inv(i, j) = -Inv(i, i) sum_{j <= k < i} L(i, k) Inv(k, j); the sum goes through Tmp(i, j), where the same
-// wavefront reads it back (LDS operations of a wavefront are in order)
+// wavefront reads it back, as it may read Inv(i, j) for a leaf further down
 __device__ inline void leaf_inverse(const float (*M)[BLD], float (*Inv)[BLD], float (*Tmp)[BLD], int i, int j) {
   floatx4 t = {0.f, 0.f, 0.f, 0.f};
   for (int k = j; k < i; ++k) leaf_ab(t, M, 16 * i, 16 * k, Inv, 16 * k, 16 * j, 1.f);
   leaf_store(Tmp, 16 * i, 16 * j, t);
+  lds_handover();
   floatx4 x = {0.f, 0.f, 0.f, 0.f};
   leaf_ab(x, Inv, 16 * i, 16 * i, Tmp, 16 * i, 16 * j, -1.f);
   leaf_store(Inv, 16 * i, 16 * j, x);
+  lds_handover();
 }
 
 // M: the block (lower triangle meaningful on entry, identity beyond nb); on exit its lower

@@ -78,6 +78,15 @@ __device__ inline void load16_to_lds(int4v rsrc, uint32_t lds_addr, uint32_t vof
 }
 __device__ inline void wait_all_loads() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
+// Between LDS stores and reads of what other lanes of the same wavefront stored: LDS operations of a wavefront are
+// carried out in order, but the compiler reasons about one lane and may exchange a store and a load whose addresses
+// differ in every lane.  No instruction comes of it.
+__device__ inline void lds_handover() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
 constexpr int64_t kAlign = 256;
 inline size_t align_up(size_t x) { return (x + (kAlign - 1)) & ~(size_t)(kAlign - 1); }
 __host__ __device__ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }

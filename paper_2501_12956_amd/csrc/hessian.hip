@@ -409,7 +409,7 @@ __global__ __launch_bounds__(64 * HNW) void hessian_f16_kernel(const _Float16* _
         for (int q4 = 0; q4 < 4; ++q4)
           *reinterpret_cast<floatx4*>(piece + l32 * TLD + q4 * 8 + kh * 4) =
               floatx4{a[4 * q4], a[4 * q4 + 1], a[4 * q4 + 2], a[4 * q4 + 3]};
-        __builtin_amdgcn_wave_barrier();
+        lds_handover();
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
           const floatx4 x = *reinterpret_cast<const floatx4*>(piece + (c * 8 + (lane >> 3)) * TLD + (lane & 7) * 4);
@@ -423,7 +423,7 @@ __global__ __launch_bounds__(64 * HNW) void hessian_f16_kernel(const _Float16* _
               if (row + u < n && col < row + u) d[u] = x[u];
           }
         }
-        __builtin_amdgcn_wave_barrier();
+        lds_handover();
       }
     };
     if (accumulate)

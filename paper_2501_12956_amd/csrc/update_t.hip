@@ -608,8 +608,8 @@ __global__ __launch_bounds__(256, 3) void t_delta_kernel(const int8_t* __restric
   };
   fetch(0);
   for (int64_t k0 = 0; k0 < npad; k0 += 128) {
-    // the lines of this batch into LDS (only this wavefront touches its stage, and its LDS
-    // operations execute in order), the one-hot operands of the batch, then the next batch's loads
+    // the lines of this batch into LDS (only this wavefront touches its stage), the one-hot operands of the batch,
+    // then the next batch's loads
 #pragma unroll
     for (int t = 0; t < 4; ++t)
 #pragma unroll
@@ -619,6 +619,7 @@ __global__ __launch_bounds__(256, 3) void t_delta_kernel(const int8_t* __restric
 #pragma unroll
     for (int t = 0; t < 4; ++t) bf[t] = onehot16(q16[t], brep, cs16[t]);
     if (k0 + 128 < npad) fetch(k0 + 128);
+    lds_handover();
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
 #pragma unroll
@@ -627,6 +628,7 @@ __global__ __launch_bounds__(256, 3) void t_delta_kernel(const int8_t* __restric
         acc[d] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, bf[t], acc[d], 0, 0, 0);
       }
     }
+    lds_handover();
   }
   // fold: row r of the tile sits in register v = 4 (r / 8) + r % 4 of the lanes with kh = (r / 4) % 2
   double R[C];
@@ -651,7 +653,7 @@ __global__ __launch_bounds__(256, 3) void t_delta_kernel(const int8_t* __restric
   double* __restrict__ Rs = reinterpret_cast<double*>(stage);        // [lane][C], 8 KB at most
 #pragma unroll
   for (int a2 = 0; a2 < C; ++a2) Rs[lane * C + a2] = R[a2];
-  __builtin_amdgcn_wave_barrier();
+  lds_handover();
   for (int e = lane; e < C * C; e += 64) {
     const int a2 = e / C, b2 = e % C;
     Dpart[(int64_t)q * C * C + e] =
