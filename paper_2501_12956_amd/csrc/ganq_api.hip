@@ -517,12 +517,13 @@ ganq_status ganq_build_hessian(ganq_ctx* ctx, const void* X, ganq_dtype x_dtype,
   ganq_status st = bind_device(ctx);
   if (st != GANQ_OK) return st;
   hipStream_t s = ctx->stream;
-  Arena ar = call_arena(ctx, x_dtype == GANQ_F16 ? hessian_scratch_bytes(n, p > 0 ? p : 1)
-                                                 : hessian_f32_scratch_bytes(n, 1));
+  const bool direct = x_dtype == GANQ_F16 && hessian_direct(n, p, ldh, accumulate);
+  const size_t need = direct ? 0 : x_dtype == GANQ_F16 ? hessian_scratch_bytes(n, p > 0 ? p : 1) : hessian_f32_scratch_bytes(n, 1);
+  Arena ar = call_arena(ctx, need);
   ProfScope prof(ctx, GANQ_K_HESSIAN);
   if (x_dtype == GANQ_F16) {
-    float* part = (float*)ar.take(hessian_scratch_bytes(n, p > 0 ? p : 1));
-    if (part == nullptr) return fail(ctx, GANQ_ERR_WORKSPACE, "workspace too small for H = X X^T");
+    float* part = direct ? nullptr : (float*)ar.take(need);
+    if (!direct && part == nullptr) return fail(ctx, GANQ_ERR_WORKSPACE, "workspace too small for H = X X^T");
     GANQ_HIP(ctx, launch_hessian_f16(s, (const _Float16*)X, n, p, ldx, H, ldh, accumulate, part));
   } else {
     const int split = fit_f32_split(n, p, ar.room());
@@ -553,8 +554,9 @@ ganq_status ganq_build_hessian_tokens(ganq_ctx* ctx, const void* Xt, ganq_dtype 
     // the product reads the token-major array as it is (transposing LDS reads): no copy
     ctx->tprep.valid = false;
     Arena ar(ctx->ws, ctx->ws_bytes);
-    float* part = (float*)ar.take(hessian_scratch_bytes(n, p));
-    if (part == nullptr) return fail(ctx, GANQ_ERR_WORKSPACE, "workspace too small for H = Xt^T Xt");
+    const bool direct = hessian_direct(n, p, ldh, accumulate);
+    float* part = direct ? nullptr : (float*)ar.take(hessian_scratch_bytes(n, p));
+    if (!direct && part == nullptr) return fail(ctx, GANQ_ERR_WORKSPACE, "workspace too small for H = Xt^T Xt");
     ProfScope prof(ctx, GANQ_K_HESSIAN);
     GANQ_HIP(ctx, launch_hessian_f16_tokens(s, (const _Float16*)Xt, n, p, ldxt, H, ldh, accumulate, part));
     ctx->last_error.clear();
@@ -579,8 +581,10 @@ ganq_status ganq_build_hessian_tokens(ganq_ctx* ctx, const void* Xt, ganq_dtype 
   if (x_dtype == GANQ_F16 && chunk > kMaxChunkF16) chunk = kMaxChunkF16;
   Arena ar(ctx->ws, ctx->ws_bytes);
   void* Xn = ar.take((size_t)n * chunk * eb);
-  float* part = (float*)ar.take(part_bytes);
-  if (Xn == nullptr || part == nullptr)
+  // a shorter chunk is split into no more runs, but every chunk after the first adds to H
+  const bool direct = x_dtype == GANQ_F16 && hessian_direct(n, chunk, ldh, accumulate != 0 || chunk < p8);
+  float* part = direct ? nullptr : (float*)ar.take(part_bytes);
+  if (Xn == nullptr || (!direct && part == nullptr))
     return fail(ctx, GANQ_ERR_WORKSPACE, "workspace too small for H = Xt^T Xt");
   ProfScope prof(ctx, GANQ_K_HESSIAN);
   for (int64_t k0 = 0; k0 < p; k0 += chunk) {

@@ -128,6 +128,8 @@ constexpr int kHessTile = 256;      // output tile edge of the fp16 H = X X^T ke
 constexpr int kHessMaxSplit = 16;   // upper bound on token-axis splits
 
 int hessian_split(int64_t n, int64_t p);
+// whether the fp16 product writes H itself and needs no partial sums
+bool hessian_direct(int64_t n, int64_t p, int64_t ldh, int accumulate);
 size_t hessian_scratch_bytes(int64_t n, int64_t p);
 int hessian_f32_split(int64_t n, int64_t p);
 size_t hessian_f32_scratch_bytes(int64_t n, int split);

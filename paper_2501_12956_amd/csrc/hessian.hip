@@ -526,9 +526,9 @@ int hessian_split(int64_t n, int64_t p) {
 // 256 17.8 / 13.6, 1024 20.3 / 17.1, 1536 (21 tiles) 20.6 / 18.9, 2047 (36) 25.9 / 25.5, 2048 21.1 / 23.6, 2304
 // 21.3 / 24.1, 4096 27.5 / 40.2; nothing held: 64 7.8 / 10.8, 96 9.7 / 11.4, 100 13.0 / 11.6, 127 13.2 / 12.0, 130
 // 11.9 / 12.1, 256 12.3 / 13.1, 1025 15.0 / 16.9, 2048 16.1 / 21.6.
-static bool hessian_direct(int64_t n, int split, int64_t ldh, int accumulate) {
+bool hessian_direct(int64_t n, int64_t p, int64_t ldh, int accumulate) {
   const int64_t nt = ceil_div(n, HT);
-  if (split != 1 || ldh > ((int64_t)1 << 20)) return false;      // 32-bit offsets inside 256 rows of H
+  if (hessian_split(n, p) != 1 || ldh > ((int64_t)1 << 20)) return false;      // 32-bit offsets inside 256 rows of H
   return accumulate ? nt * (nt + 1) / 2 >= 36 : n <= HT / 4 || n >= HT / 2;
 }
 
@@ -556,7 +556,7 @@ hipError_t launch_hessian_f16(hipStream_t s, const _Float16* X, int64_t n, int64
                               float* H, int64_t ldh, int accumulate, float* partials) {
   if (ldx >= ((int64_t)1 << 22) || (p % 8) != 0 || (ldx % 8) != 0) return hipErrorInvalidValue;
   const int split = hessian_split(n, p);
-  const bool direct = hessian_direct(n, split, ldh, accumulate);
+  const bool direct = hessian_direct(n, p, ldh, accumulate);
   const int64_t chunk = ceil_div(ceil_div(p, split), HCHUNK) * HCHUNK;
   const int64_t nt = ceil_div(n, HT);
   const int ntiles = (int)(nt * (nt + 1) / 2);
@@ -592,7 +592,7 @@ hipError_t launch_hessian_f16_tokens(hipStream_t s, const _Float16* Xt, int64_t 
                                      float* H, int64_t ldh, int accumulate, float* partials) {
   if (!hessian_tokens_direct_ok(Xt, n, p, ldxt)) return hipErrorInvalidValue;
   const int split = hessian_split(n, p);
-  const bool direct = hessian_direct(n, split, ldh, accumulate);
+  const bool direct = hessian_direct(n, p, ldh, accumulate);
   const int64_t chunk = ceil_div(ceil_div(p, split), HCHUNK) * HCHUNK;
   const int64_t nt = ceil_div(n, HT);
   const int ntiles = (int)(nt * (nt + 1) / 2);

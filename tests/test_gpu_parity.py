@@ -1298,6 +1298,45 @@ def test_hessian_fp32_takes_the_splits_its_workspace_holds():
     c.close()
 
 
+def test_hessian_that_is_written_directly_needs_no_partial_sums():
+    """Products whose tokens are not split write H themselves: no workspace for feature-major tokens and aligned
+    token-major ones, the transposed copy for others.  Those that take a second kernel (few tiles onto H, split
+    tokens) are refused without room for the partial sums."""
+    from paper_2501_12956_amd import binding as b
+    g = torch.Generator(device="cuda").manual_seed(3)
+
+    def call(c, X, H, acc, tokens):
+        fn = c.lib.ganq_build_hessian_tokens if tokens else c.lib.ganq_build_hessian
+        n, p = (X.shape[1], X.shape[0]) if tokens else X.shape
+        return fn(c.handle, X.data_ptr(), 0, n, p, X.stride(0), H.data_ptr(), H.stride(0), acc)
+
+    for n, p in ((300, 64), (2304, 64)):
+        X = torch.randint(-3, 4, (n, p), generator=g, device="cuda")
+        want = (X.float() @ X.float().t())
+        Xh, Xt = X.half().contiguous(), X.t().half().contiguous()
+        H = torch.empty(n, n, device="cuda")
+        c = b.Context(0)                                     # no workspace set
+        onto = b.GANQ_OK if n > 2000 else b.GANQ_ERR_WORKSPACE
+        assert call(c, Xh, H, 0, False) == b.GANQ_OK and torch.equal(H, want)
+        assert call(c, Xh, H, 1, False) == onto and torch.equal(H, want * (2 if onto == b.GANQ_OK else 1))
+        if n % 8 == 0:
+            assert call(c, Xt, H, 0, True) == b.GANQ_OK and torch.equal(H, want)
+            assert call(c, Xt, H, 1, True) == onto and torch.equal(H, want * 2)
+        else:
+            assert call(c, Xt, H, 0, True) == b.GANQ_ERR_WORKSPACE
+        c.close()
+        Xo = torch.zeros(p, n + 1, dtype=torch.float16, device="cuda")
+        Xo[:, :n] = Xt                                       # rows off 16 bytes: transposed
+        c, ws = _raw_context(n * p * 2 // 256 * 256 + 256)
+        assert call(c, Xo[:, :n], H, 0, True) == b.GANQ_OK and torch.equal(H, want)
+        assert call(c, Xo[:, :n], H, 1, True) == onto and torch.equal(H, want * (2 if onto == b.GANQ_OK else 1))
+        c.close()
+    X = torch.ones(300, 8192, dtype=torch.float16, device="cuda")         # split into runs of tokens
+    c = b.Context(0)
+    assert call(c, X, torch.empty(300, 300, device="cuda"), 0, False) == b.GANQ_ERR_WORKSPACE
+    c.close()
+
+
 @pytest.mark.parametrize("m,n,nbits,given_L", [(40, 200, 4, False), (33, 1100, 3, False), (70, 2100, 4, False), (300, 1300, 2, True)])
 def test_quantize_layer_in_exactly_the_workspace_it_asks_for(ctx, m, n, nbits, given_L):
     """The buffers that share space inside the call (factorization, S-update) do not change its results."""
