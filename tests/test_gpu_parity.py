@@ -13,6 +13,8 @@ Tolerances (derived from the arithmetic of the kernels):
   T        per row |dT|_inf <= 1e-4 |T|_inf
   loss     1e-4 relative
 """
+import functools
+
 import numpy as np
 import pytest
 import torch
@@ -1120,18 +1122,71 @@ def test_update_T_at_the_edges_of_slabs_and_stages(ctx, m, n, nbits):
     assert err.max() <= 1e-4, err.max()
 
 
-@pytest.mark.parametrize("m,n,nbits,kind", [(33, 2049, 4, "weak"), (16, 2176, 3, "weak"), (70, 2303, 2, "weak"),
-                                            (130, 2050, 1, "weak"), (20, 2100, 4, "wide"), (17, 6145, 4, "weak")])
+@functools.lru_cache(maxsize=2)
+def _two_digit_H(n, seed):
+    """A second-moment matrix all of whose entries take two digits of the T-update's integers: correlations within
+    +-1/40, feature scales within a factor of two but for every 97th, 16 times as large."""
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    R = torch.rand(n, n, generator=g, device="cuda") - 0.5
+    H = (R + R.t()) * 0.025
+    H.fill_diagonal_(1.0)
+    d = 1.0 + torch.rand(n, generator=g, device="cuda")
+    d[::97] *= 16.0
+    return (H * d[:, None] * d[None, :]).cpu().numpy()
+
+
+def _both_digits_at_once(H):
+    """Whether the refit multiplies both digits of H in one pass: the rule of the preparing kernels, replayed.  Every
+    row of every tile of 128 asks for two digits, no subset sum of a row's integers leaves 31 bits, and the row
+    exponents of a tile lie within six of each other."""
+    H = np.abs(H.astype(np.float64))
+    n = len(H)
+    d = np.diag(H).copy()
+    np.fill_diagonal(H, 0.0)
+    live = d > 0
+    e = np.zeros(n)
+    e[live] = np.clip(6 + np.rint(0.5 * np.log2(d[live] / d.max())), 0, 6)
+    g = max((np.sqrt(d[live]) / 2.0 ** e[live]).min(), np.sqrt(d.max()) * 2.0 ** -18)
+    mx, total = (H / 2.0 ** e).max(axis=1), H.sum(axis=1)
+    rows = mx > 0
+    s = np.zeros(n, int)
+    s[rows] = 14 - np.floor(np.log2(mx[rows])).astype(int)
+    s[rows & (np.ldexp(mx, s) > 32512)] -= 1
+    two = 16 * mx <= np.sqrt(d) * g
+    fits = np.ones(n, bool)
+    fits[rows] = s[rows] <= 29 - np.floor(np.log2(total[rows])).astype(int)
+    near = all(np.ptp(s[j:j + 128][rows[j:j + 128]]) <= 6 for j in range(0, n, 128) if rows[j:j + 128].any())
+    return bool(two[rows].all() and fits.all() and near)
+
+
+def _refit64(W, H, Q, nbits):
+    """All rows of the least-squares refit in float64 on the GPU; every code occurs in every row."""
+    W, H, Q, C = dev(W).double(), dev(H).double(), dev(Q).long(), 1 << nbits
+    G, T = W @ H, torch.empty(W.shape[0], C, dtype=torch.float64, device="cuda")
+    for i in range(0, len(W), 32):
+        S = torch.nn.functional.one_hot(Q[i:i + 32], C).double()                       # rows, n, C
+        HS = (H @ S.permute(1, 0, 2).reshape(len(H), -1)).reshape(len(H), -1, C)
+        A = torch.stack([S[r].t().contiguous() @ HS[:, r].contiguous() for r in range(len(S))])
+        T[i:i + 32] = torch.linalg.solve(A, torch.stack([S[r].t().contiguous() @ G[i + r] for r in range(len(S))]))
+    return T.cpu().numpy()
+
+
+@pytest.mark.parametrize("m,n,nbits,kind", [(33, 2049, 4, "two"), (16, 2176, 3, "two"), (70, 2303, 2, "two"),
+                                            (130, 2050, 1, "two"), (17, 6145, 4, "two"), (200, 6145, 4, "two"),
+                                            (400, 6145, 3, "two"), (780, 6145, 2, "two"), (1560, 6145, 1, "two"),
+                                            (220, 6400, 4, "two"), (20, 2100, 4, "wide"), (33, 2049, 3, "weak")])
 def test_update_T_both_digits_at_once(ctx, m, n, nbits, kind):
-    """Long sums go to a kernel that multiplies both digits of H in one pass, if every tile has two: odd and
-    even numbers of row tiles, more and less than one item per workgroup, row scales that differ within a
-    tile (several factors in the fold), and a matrix that needs more digits after all."""
-    H32 = _structured_H(kind, n, 31)
+    """Long sums go to a kernel that multiplies both digits of H in one pass, if every tile has two: odd and even
+    numbers of row tiles; fewer items than workgroups, and (n >= 6144 and 13 or 14 slabs of rows) one to two items a
+    workgroup, the last ones uneven; three, four and five stages; row scales that differ within a tile (several factors
+    in the fold); and matrices that need more digits after all.  All rows, against float64."""
+    H32 = _two_digit_H(n, 31) if kind == "two" else _structured_H(kind, n, 31)
+    assert _both_digits_at_once(H32) == (kind == "two")
     rng = np.random.default_rng(32)
     W = (rng.standard_normal((m, n)) * 0.02).astype(np.float32)
     Q = rng.integers(0, 1 << nbits, size=(m, n)).astype(np.uint8)
     Tg = ctx.update_T(dev(W), dev(H32), dev(Q), dev(np.zeros((m, 1 << nbits), np.float32)), nbits).cpu().numpy()
-    Tref, _ = ref.update_T(W.astype(np.float64), H32.astype(np.float64), Q, nbits)
+    Tref = _refit64(W, H32, Q, nbits)
     err = np.abs(Tg - Tref).max(axis=1) / np.abs(Tref).max(axis=1)
     assert err.max() <= 1e-4, err.max()
 
@@ -1142,12 +1197,13 @@ def test_update_T_rows_without_entries(ctx, m, n, nbits, power):
     at any exponent: some in each tile, a whole tile, the last row (alone in its tile for some n), with H far
     from unit scale.  The refit does not depend on a power of two in H, so the oracle's bound is that of the
     other tests of these sums."""
-    H32 = _structured_H("weak", n, 33)
+    H32 = _two_digit_H(n, 33).copy() if n >= 2048 else _structured_H("weak", n, 33)      # two digits, or three
     gone = [j for j in range(n) if j % 61 == 7 or 128 <= j < 256 or j == n - 1]
     H32[gone, :] = 0
     H32[:, gone] = 0
     H32[200, 200] = H32[0, 0]                         # a feature that meets no other
     H32 = np.ldexp(H32, power).astype(np.float32)
+    assert _both_digits_at_once(H32) == (n >= 2048)
     rng = np.random.default_rng(34)
     W = (rng.standard_normal((m, n)) * 0.02).astype(np.float32)
     Q = rng.integers(0, 1 << nbits, size=(m, n)).astype(np.uint8)
