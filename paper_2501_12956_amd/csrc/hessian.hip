@@ -125,7 +125,7 @@ __device__ inline void zorder_tile(int t, int nt, int& bm, int& bn) {
 // 128 x 128 took 1205 (1105) us.
 //
 // TOK: X is the token-major array Xt (p x n, tokens x features, leading dimension ldx) and
-// H = Xt^T Xt.  A stage then holds 64 token rows of 256 features per operand (512-byte rows), and
+// H = Xt^T Xt.  A stage then holds 32 token rows of 256 features per operand (512-byte rows), and
 // the MFMA fragments - 8 consecutive tokens of one feature per lane - are gathered by the LDS
 // transpose reads of gfx950 (ds_read_b64_tr_b16: within 16 lanes, lane 4a + b receives element b of
 // the 8-byte pieces addressed by lanes a, 4 + a, 8 + a, 12 + a).  Lane 4e + a of a group of 16
@@ -249,7 +249,7 @@ __global__ __launch_bounds__(64 * HNW) void hessian_f16_kernel(const _Float16* _
 
   const int rswz = (l32 >> 1) & 7;
   // TOK: byte offset, inside a stage, of this lane's 8-byte piece for each of the wavefront's
-  // fragments: token row 8 (lane / 32) + e, chunk (feature / 8) ^ 2 e, half chunk a & 1
+  // fragments: token row 8 (lane / 32) + e, chunk (feature / 8) ^ 4 e, half chunk a & 1
   uint32_t toffA[4], toffB[2];
   {
     const int s16 = lane & 15, e = s16 >> 2, a = s16 & 3, g1 = (lane >> 4) & 1;
@@ -352,7 +352,7 @@ __global__ __launch_bounds__(64 * HNW) void hessian_f16_kernel(const _Float16* _
 
   if (direct) {
     // The tile's sums are complete and go to both triangles of H from here: 8 calls of 2048 tokens at n =
-    // 4096 took 66 + 26 us each with the second kernel, now 76.  What H held is requested three 32 x 32 tiles
+    // 4096 took 66 + 26 us each with the second kernel, now 70.  What H held is requested three 32 x 32 tiles
     // ahead (one tile at a time the loads alone take 25 us), without branches, so that a wait can be for the oldest
     // (64 tokens onto H, n = 2304: 23.6 us with branches, 21.3 without), and the mirrored elements are turned in a
     // piece of LDS of the wavefront's own, so that they leave as whole lines (16-byte runs straight from the
@@ -581,7 +581,7 @@ hipError_t launch_hessian_f16(hipStream_t s, const _Float16* X, int64_t n, int64
 // of features, and a token split whose byte extent fits the 32-bit offsets of the loads.
 bool hessian_tokens_direct_ok(const void* Xt, int64_t n, int64_t p, int64_t ldxt) {
   if (p <= 0 || (((uintptr_t)Xt) & 15) != 0 || (ldxt % 8) != 0 || (n % 8) != 0) return false;
-  if (ldxt >= ((int64_t)1 << 23)) return false;       // 64 token rows within 31-bit lane offsets
+  if (ldxt >= ((int64_t)1 << 23)) return false;       // 32 token rows within 31-bit lane offsets
   const int split = hessian_split(n, p);
   const int64_t chunk = ceil_div(ceil_div(p, split), HCHUNK) * HCHUNK;
   return (chunk + HCHUNK) * ldxt * 2 <= ((int64_t)1 << 31);

@@ -1121,8 +1121,10 @@ __global__ __launch_bounds__(64 * TNW, 2) void t_accum_kernel(const int8_t* __re
 // is energy, and energy is what bounds a long sum: at 8192 x 28672 the sweep takes 65.6 ms (70.8 with a pass
 // per digit), 4096 x 11008 5.9 ms (6.1).  A lone wavefront per SIMD has to do everything under its own MFMAs (2400
 // cycles a stage, 2048 of them MFMAs), so shorter sums gain less than the second launch costs (t_two_digits).
-// A workgroup takes its items one after the other, and a stage is requested NS - 1 stages ahead across tiles
-// and items, so that nothing drains at their ends.
+// A workgroup takes its items one after the other, and a stage is requested NS - 1 stages ahead across tiles and
+// items.  Once a row tile they are drained all the same: the fold leaves no registers for the fragments and the one-hot
+// words read ahead, which go to scratch (73 registers at 4 bits, 106, 105 and 129 at 3, 2 and 1), and the wait for
+// their return is one for every load.  Little of 112 stages a tile, more of the 8 to 24 of n = 2048 to 6144.
 constexpr int TKS = 128;                     // k per stage: a row tile has one stage per tile left of it
 constexpr int D_ROWB = TKS;
 constexpr int D_ATILEB = TM * D_ROWB;
