@@ -1824,6 +1824,7 @@ inline size_t t_layout(int64_t m, int64_t n, int nbits, char* base, TScratch* ou
   const size_t o_diag = take((size_t)n * sizeof(float));
   const size_t o_cs = take((size_t)npad);
   const size_t o_wj = take((size_t)npad * sizeof(float));
+  // in this order: one descriptor of t_accum_kernel spans S2, S3 and the factors over Sneed
   const size_t o_s2 = take((size_t)npad);
   const size_t o_s3 = take((size_t)npad);
   const size_t o_sn = take((size_t)npad * sizeof(int16_t));
